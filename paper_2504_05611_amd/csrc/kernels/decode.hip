@@ -40,6 +40,7 @@
 
 #include "../host/device.h"
 #include "../host/timing.h"
+#include "bp_chunk.h"
 #include "decoder.h"
 
 namespace tmcs {
@@ -73,14 +74,13 @@ struct DecodeDevice {
     float* lamp = nullptr;
     int32_t Mpk4 = 0, Npk = 0;
     int32_t Kc4 = 0, Kv4 = 0;        // list lengths rounded up to BP_AHEAD (arrays: [K4 + BP_AHEAD][P])
-    // the LDS flavour (longest-processing-time lists of get_sched; checks numbered
-    // in the order the lanes first reach them, columns i P + l; int2 records)
-    int2 *pcL = nullptr, *pvL = nullptr;
-    int32_t *pceL = nullptr, *pveL = nullptr, *vmapL = nullptr, *corigL = nullptr;
-    int4* pinitL = nullptr;
-    int32_t MpkL = 0, NpkL = 0;
   };
   std::vector<Sched> scheds;
+  std::vector<ChunkSched> chunks;   // schedules of the LDS-state kernel, one per team size used so far
+  double log_start = 30.0;          // log10 of the largest magnitude BP starts from
+  int chunk_P = 0;                  // its default team size (-1: the state does not fit)
+  float* cw = nullptr;              // per-edge weights by schedule step
+  size_t cap_cw = 0;
   // scratch
   int32_t* counters = nullptr;     // [0] queue len, [1] bp next, [2] osd len, [3] osd next
   int32_t* queue = nullptr;
@@ -208,14 +208,14 @@ __global__ void __launch_bounds__(256) k_compact_wide(const uint64_t* __restrict
   }
 }
 
-// BP over persistent teams: one workgroup (a "team" of P = blockDim.x lanes)
-// decodes one shot at a time, with the whole per-shot state in LDS.  Work is
-// split over the lanes by static schedules built once per DEM and team size
-// (longest-processing-time assignment of whole checks, and of whole columns,
-// to lanes), so every step of a pass is one edge per lane with no intra-pass
-// synchronisation; a pass ends with one barrier.
+// BP over persistent teams with a shot's state in device memory, for DEMs whose
+// state does not fit in LDS (bp_chunk.hip decodes the others): one workgroup (a
+// "team" of P = blockDim.x lanes) decodes one shot at a time in its slab
+// (a.gstate + blockIdx.x * a.team_bytes).  Work is split over the lanes by static
+// schedules built once per DEM and team size, so every step of a pass is one edge
+// per lane with no intra-pass synchronisation; a pass ends with one barrier.
 //
-// Per-shot LDS state (compressed): for every check (n1, n2) = the two smallest
+// Per-shot state (compressed): for every check (n1, n2) = the two smallest
 // |q_{v->c}|, the argmin edge, the sign parity of the q's and the syndrome bit;
 // one sign byte per edge (sign of q_{v->c}); L_v per column.  Messages are
 // rebuilt from it: m_{c->v} = (-1)^{s_c + parity + sgn q_e} alpha_t(e) *
@@ -227,17 +227,13 @@ __global__ void __launch_bounds__(256) k_compact_wide(const uint64_t* __restrict
 // writes them with the record, and both passes read a message's sign from the
 // record they already load.  The argmin edge is kept as 2 + its position.
 // Checks and columns are renumbered (c', v': the state and L slots in the
-// order the lanes reach them) and the schedules hold 8-byte records, half the
-// schedule bytes a team streams per iteration; the CSR edge of a record (for
-// per-edge weights) comes from arrays of its own.  Results are the same.
+// order the lanes reach them) and the schedules hold 4-byte records; the CSR
+// edge of a record (for per-edge weights) comes from arrays of its own.
 //
 // Iteration 1 needs no check pass: with q_{v->c} = lambda_v its state depends
 // on the DEM alone (precomputed, plus the syndrome bit).  Iteration t is then a
 // variable pass (L^t) followed by a check pass that tests H [L^t < 0] = s and,
 // if t < T, builds the state of iteration t + 1.
-// GSTATE: the per-shot state lives in this team's slab of device memory
-// (a.gstate + blockIdx.x * a.team_bytes) instead of LDS, for DEMs whose state
-// does not fit; the code is otherwise the same.
 //
 // MULTI: one launch decodes the queued shots of several decode items (a plan's
 // instances, each with its own DEM, schedules, state and outputs): job g of a
@@ -247,36 +243,23 @@ __global__ void __launch_bounds__(256) k_compact_wide(const uint64_t* __restrict
 // team switches at most once per item; its statistics go to the item they
 // belong to.  Weights are then per item (weights may be null: scalar alpha).
 
-template <bool WEIGHTED, bool GSTATE, bool MULTI, bool PK>
+template <bool WEIGHTED, bool MULTI, bool PK>
 __global__ void __launch_bounds__(1024) k_bp(BPArgs a, BPMulti mu) {
-  extern __shared__ __align__(16) unsigned char sm[];
   unsigned char* base = nullptr;
-  float4* state = nullptr;                            // [m + 1] (slot m: padding records); PK: [Mpk + 2] (LDS: [Mpk + 1])
+  float4* state = nullptr;                            // [m + 1] (slot m: padding records); PK: [Mpk + 2]
   float* L = nullptr;                                 // [n]; PK: [Npk + 1] (slot Npk: +BIG for no-op edges)
   uint8_t* sgn = nullptr;                             // [E4 + 4] (byte E4: padding records); !PK only
   auto bind = [&]() {
-    base = GSTATE ? a.gstate + (size_t)blockIdx.x * a.team_bytes : sm;
+    base = a.gstate + (size_t)blockIdx.x * a.team_bytes;
     state = (float4*)base;
-    L = (float*)(state + (PK ? (GSTATE ? a.Mpk + 2 : a.Mpk + 1) : a.m + 1));
+    L = (float*)(state + (PK ? a.Mpk + 2 : a.m + 1));
     sgn = (uint8_t*)(L + a.n);
   };
-  // state and L accesses (device memory: kept global in a multi launch, whose slab pointer is read from memory)
-  auto ld_state = [&](int c) -> float4 {
-    if constexpr (GSTATE) return gload(state + c);
-    else return state[c];
-  };
-  auto st_state = [&](int c, const float4 x) {
-    if constexpr (GSTATE) gstore(state + c, x);
-    else state[c] = x;
-  };
-  auto ld_L = [&](int v) -> float {
-    if constexpr (GSTATE) return gload(L + v);
-    else return L[v];
-  };
-  auto st_L = [&](int v, const float x) {
-    if constexpr (GSTATE) gstore(L + v, x);
-    else L[v] = x;
-  };
+  // state and L accesses (kept global in a multi launch, whose slab pointer is read from memory)
+  auto ld_state = [&](int c) -> float4 { return gload(state + c); };
+  auto st_state = [&](int c, const float4 x) { gstore(state + c, x); };
+  auto ld_L = [&](int v) -> float { return gload(L + v); };
+  auto st_L = [&](int v, const float x) { gstore(L + v, x); };
   // schedule records and weights (a multi launch reads their pointers from memory)
   auto rec = [&](const auto* p) {
     if constexpr (MULTI) return gload(p);
@@ -358,8 +341,8 @@ __global__ void __launch_bounds__(1024) k_bp(BPArgs a, BPMulti mu) {
       if constexpr (PK) {
         // (L needs no start value: the variable pass writes every slot the check
         // pass reads, but slot Npk, which no-op check edges read)
-        if (GSTATE && tid == 0) st_L(a.Npk, BP_BIG);
-        for (int c = tid; c < (GSTATE ? a.Mpk + 2 : a.Mpk); c += P) {
+        if (tid == 0) st_L(a.Npk, BP_BIG);
+        for (int c = tid; c < a.Mpk + 2; c += P) {
           int4 s0 = gload(a.pinit + c);
           const int co = gload(a.corig + c);          // (-1: an empty, padding or sink slot)
           const int sb = co < 0 ? 0 : (int)((gload(sy + (co >> 6)) >> (co & 63)) & 1ull);
@@ -378,10 +361,10 @@ __global__ void __launch_bounds__(1024) k_bp(BPArgs a, BPMulti mu) {
           const int sb = (int)((sy[c >> 6] >> (c & 63)) & 1ull);
           fl |= sb | ((s0.z < 0 && sb) ? 2 : 0);   // bit 1: a check without edges can never be satisfied
           s0.w |= sb << 1;
-          state[c] = make_float4(__int_as_float(s0.x), __int_as_float(s0.y), __int_as_float(s0.z),
-                                 __int_as_float(s0.w));
+          st_state(c, make_float4(__int_as_float(s0.x), __int_as_float(s0.y), __int_as_float(s0.z),
+                                  __int_as_float(s0.w)));
         }
-        for (int v = tid; v < a.n; v += P) L[v] = a.lam[v];
+        for (int v = tid; v < a.n; v += P) st_L(v, a.lam[v]);
         for (int i = tid; i < (a.E4 >> 2); i += P) ((uint32_t*)sgn)[i] = a.sign0[i];
       }
       if (fl) atomicOr(&s_flag, fl);
@@ -394,7 +377,7 @@ __global__ void __launch_bounds__(1024) k_bp(BPArgs a, BPMulti mu) {
       conv = false;
       for (int t = 1;; ++t) {
         // variable pass: L^t from the state of iteration t
-        if constexpr (PK && GSTATE) {
+        if constexpr (PK) {
           // degree chunks: a column's first and last edge are on the same step
           // in every lane of the wave, so those branches are uniform (lane 0's
           // flags).  BP_AHEAD steps' loads go out before any of their stores (the
@@ -405,7 +388,7 @@ __global__ void __launch_bounds__(1024) k_bp(BPArgs a, BPMulti mu) {
           int vo = tid;                                   // v' of the lane's current column
           const int32_t* rp = a.pvs4 + tid;
           const int32_t* ep = a.pve + tid;
-          constexpr int U = GSTATE ? BP_AHEAD : 2;   // (LDS: two steps, fewer registers)
+          constexpr int U = BP_AHEAD;
           int r[U];
           int ev[U];
 #pragma unroll
@@ -441,39 +424,6 @@ __global__ void __launch_bounds__(1024) k_bp(BPArgs a, BPMulti mu) {
               if (use_w) ev[u] = rec(ep + (size_t)(k + U + u) * P);
             }
           }
-        } else if constexpr (PK) {
-          // state in LDS: per-lane flags, int2 records read two steps ahead (the
-          // schedule holds two rows of padding past its even length)
-          const float* wt = use_w ? a.w + (int64_t)(t - 1) * a.E : nullptr;
-          float acc = 0.0f;
-          int vo = tid;                                   // v' of the lane's current column
-          // x: the record's flag word; lam = lambda_v (read on a column's first edge)
-          auto vstep = [&](const int x, const float lam, const int e, const float4 s) {
-            const int sh = (x >> R_SH) & 31;
-            const float at = use_w ? rec(wt + e) : a.alpha;
-            const float mag = __fmul_rn(at, sh == __float_as_int(s.z) ? s.y : s.x);
-            const float base = (x & R_FIRST) ? lam : acc;   // lambda_v on a column's first edge
-            acc = __fadd_rn(base, ((__float_as_int(s.w) >> sh) & 1) ? -mag : mag);
-            if (x & R_LAST) {
-              st_L(vo, acc);
-              vo += P;
-            }
-          };
-          const int32_t* ep = a.pve + tid;
-          {
-            const int2* rp = a.pvs + tid;
-            int2 ra = rec(rp), rb = rec(rp + P);
-            int ea = 0, eb = 0;
-            if (use_w) { ea = rec(ep); eb = rec(ep + P); }
-            for (int k = 0; k < a.Kv; k += 2) {
-              vstep(ra.x, __int_as_float(ra.y), ea, state[ra.x & R_IDX]);
-              ra = rec(rp + (size_t)(k + 2) * P);
-              if (use_w) ea = rec(ep + (size_t)(k + 2) * P);
-              vstep(rb.x, __int_as_float(rb.y), eb, state[rb.x & R_IDX]);
-              rb = rec(rp + (size_t)(k + 3) * P);
-              if (use_w) eb = rec(ep + (size_t)(k + 3) * P);
-            }
-          }
         } else {
           const float* wt = use_w ? a.w + (int64_t)(t - 1) * a.E : nullptr;
           float acc = 0.0f;
@@ -507,25 +457,20 @@ __global__ void __launch_bounds__(1024) k_bp(BPArgs a, BPMulti mu) {
           float n1o = 0.0f, n2o = 0.0f, n1 = BP_BIG, n2 = BP_BIG;
           int nago = -1, nag = -1, sc = 0, spo = 0, npar = 0, hard = 0;
           int flo = 0, nbits = 0;                        // PK: the old record's word, the new message signs
-          // x: the record's flag word; e: the CSR edge (PK: for the weights only);
-          // get_s() gives the check's state (called on a check's first edge only),
-          // get_L() gives L_v
-          auto cstep = [&](const int x, const int c, const int e, auto&& get_s, auto&& get_L) {
+          // x: the record's flag word; c: the check; e: the CSR edge
+          auto cstep = [&](const int x, const int c, const int e) {
             const bool first = (x & R_FIRST) != 0;
-            const int sh = (x >> R_SH) & 31;
-            const int key = PK ? sh : e;                 // how the check state names its argmin edge
             // only lanes that start a check read its state (the others carry it)
             if (first) {
-              const float4 s = get_s();
+              const float4 s = ld_state(c);
               const int fl = __float_as_int(s.w);
               n1o = s.x;
               n2o = s.y;
               nago = __float_as_int(s.z);
               sc = (fl >> 1) & 1;
               spo = fl & 1;
-              flo = fl;
             }
-            const float Lv = get_L();
+            const float Lv = ld_L(x & R_IDX);
             n1 = first ? BP_BIG : n1;
             n2 = first ? BP_BIG : n2;
             nag = first ? -1 : nag;
@@ -533,32 +478,24 @@ __global__ void __launch_bounds__(1024) k_bp(BPArgs a, BPMulti mu) {
             hard = (first ? 0 : hard) ^ (Lv < 0.0f ? 1 : 0);
             if (update) {
               const float ao = use_w ? rec(wo + (e < a.E32 ? e : 0)) : a.alpha;
-              const float mag = __fmul_rn(ao, key == nago ? n2o : n1o);
-              int neg;
-              if constexpr (PK) neg = (flo >> sh) & 1;
-              else neg = sc ^ spo ^ sgn[e];
+              const float mag = __fmul_rn(ao, e == nago ? n2o : n1o);
+              const int neg = sc ^ spo ^ sgn[e];
               const float q = __fsub_rn(Lv, neg ? -mag : mag);   // q = L_v - m_old
               const float aq = fabsf(q);
               const int ng = q < 0.0f ? 1 : 0;
               const bool lt1 = aq < n1, lt2 = aq < n2;
               n2 = lt1 ? n1 : (lt2 ? aq : n2);
               n1 = lt1 ? aq : n1;
-              nag = lt1 ? key : nag;
+              nag = lt1 ? e : nag;
               npar ^= ng;
-              if constexpr (PK) nbits = (first ? 0 : nbits) | (ng << sh);
-              else sgn[e] = (uint8_t)ng;
+              sgn[e] = (uint8_t)ng;
             }
             if (x & R_LAST) {
               unsat |= hard != sc;
-              if (update) {
-                // PK: message sign of edge j = s_c + parity + sgn q_j (mod 2)
-                const int w = PK ? ((sc << 1) | ((nbits ^ ((sc ^ npar) ? (int)0xFFFFFFFCu : 0)) & (int)0xFFFFFFFCu))
-                                 : ((sc << 1) | npar);
-                st_state(c, make_float4(n1, n2, __int_as_float(nag), __int_as_float(w)));
-              }
+              if (update) st_state(c, make_float4(n1, n2, __int_as_float(nag), __int_as_float((sc << 1) | npar)));
             }
           };
-          if constexpr (PK && GSTATE) {
+          if constexpr (PK) {
             // degree chunks: a check's first and last edge are on the same step in
             // every lane of the wave, so those branches are uniform (lane 0's
             // flags) and the check states are read and written a whole wave at a
@@ -567,7 +504,7 @@ __global__ void __launch_bounds__(1024) k_bp(BPArgs a, BPMulti mu) {
             // the pass).
             const int32_t* rp = a.pcs4 + tid;
             const int32_t* ep = a.pce + tid;
-            constexpr int U = GSTATE ? BP_AHEAD : 2;   // (LDS: two steps, fewer registers)
+            constexpr int U = BP_AHEAD;
             int r[U];
             int ev[U];
 #pragma unroll
@@ -633,30 +570,13 @@ __global__ void __launch_bounds__(1024) k_bp(BPArgs a, BPMulti mu) {
                 if (use_w) ev[u] = rec(ep + (size_t)(k + U + u) * P);
               }
             }
-          } else if constexpr (PK) {
-            // state in LDS: per-lane flags, int2 records read two steps ahead
-            const int32_t* ep = a.pce + tid;
-            {
-              const int2* rp = a.pcs + tid;
-              int2 ra = rec(rp), rb = rec(rp + P);
-              int ea = 0, eb = 0;
-              if (use_w) { ea = rec(ep); eb = rec(ep + P); }
-              for (int k = 0; k < a.Kc; k += 2) {
-                cstep(ra.x, ra.y, ea, [&] { return state[ra.y]; }, [&] { return L[ra.x & R_IDX]; });
-                ra = rec(rp + (size_t)(k + 2) * P);
-                if (use_w) ea = rec(ep + (size_t)(k + 2) * P);
-                cstep(rb.x, rb.y, eb, [&] { return state[rb.y]; }, [&] { return L[rb.x & R_IDX]; });
-                rb = rec(rp + (size_t)(k + 3) * P);
-                if (use_w) eb = rec(ep + (size_t)(k + 3) * P);
-              }
-            }
           } else {
             const int4* rp = a.csched + tid;
             int4 ra = rec(rp), rb = rec(rp + P);
             for (int k = 0; k < a.Kc; k += 2) {
-              cstep(ra.x, ra.z, ra.y, [&] { return ld_state(ra.z); }, [&] { return ld_L(ra.x & R_IDX); });
+              cstep(ra.x, ra.z, ra.y);
               ra = rec(rp + (size_t)(k + 2) * P);
-              cstep(rb.x, rb.z, rb.y, [&] { return ld_state(rb.z); }, [&] { return ld_L(rb.x & R_IDX); });
+              cstep(rb.x, rb.z, rb.y);
               rb = rec(rp + (size_t)(k + 3) * P);
             }
           }
@@ -679,7 +599,7 @@ __global__ void __launch_bounds__(1024) k_bp(BPArgs a, BPMulti mu) {
         const int vm = gload(a.vmap + v);
         Lv = (vm >= 0 && (f0 & 1)) ? ld_L(vm) : gload(a.lam + v);   // (no BP run: the priors)
       } else {
-        Lv = L[v];
+        Lv = ld_L(v);
       }
       if (pos < 0 && Lv < 0.0f)
         for (int w = 0; w < a.ow; ++w) pm[w] ^= a.obs_mask[(int64_t)w * a.n + v];
@@ -735,9 +655,10 @@ void free_device(DecodeDevice* d) {
   for (auto& q : d->scheds) {
     hipFree(q.c); hipFree(q.v); hipFree(q.f);
     hipFree(q.pce); hipFree(q.pve); hipFree(q.vmap);
-    hipFree(q.pcL); hipFree(q.pvL); hipFree(q.pceL); hipFree(q.pveL); hipFree(q.vmapL); hipFree(q.corigL); hipFree(q.pinitL);
     hipFree(q.pc4); hipFree(q.pv4); hipFree(q.corig4); hipFree(q.pinit4); hipFree(q.lamp);
   }
+  for (auto& q : d->chunks) free_chunk_sched(&q);
+  hipFree(d->cw);
   *d = DecodeDevice();
 }
 
@@ -792,6 +713,13 @@ tmcs_status build_state(const Dem& D, int dev, DecodeDevice** out) {
     r.z = nag < 0 ? -1 : 2 + (nag - D.row_ptr[c]);
     r.w = (int32_t)pw;
     init_pk[c] = r;
+  }
+  {
+    double start = 1.0;
+    for (float x : lam) start = std::max(start, (double)std::fabs(x));
+    for (int c = 0; c < D.rows; ++c)
+      if (D.row_ptr[c + 1] - D.row_ptr[c] == 1) start = std::max(start, 1e30);
+    d->log_start = std::log10(start);
   }
   if (d->max_row_deg <= PK_MAX_DEG && D.cols < R_IDX && D.rows < R_IDX) d->init_pk = init_pk;
   // checks without edges (a shot with such a detection event never satisfies
@@ -980,84 +908,6 @@ tmcs_status get_fsched(const Dem& D, DecodeDevice* d, int P, int mode, DecodeDev
   return TMCS_OK;
 }
 
-// Records of the packed-state team kernel with its state in LDS, for team size
-// P: the longest-processing-time lane lists of get_sched; checks numbered in the
-// order the lanes first reach them (step i of lane l before step i of lane
-// l + 1, before step i + 1), the i-th column of lane l at v' = i P + l; int2
-// records {v' | position | flags, c'} and {c' | position | flags, lambda_v}.
-// (The degree chunks of get_psched pad small DEMs too much: on the d = 5 and
-// d = 11 surface-code DEMs they made this kernel 23-29 % slower.)
-tmcs_status get_psched_lds(const Dem& D, DecodeDevice* d, int P, int mode, DecodeDevice::Sched* out) {
-  tmcs_status st = get_sched(D, d, P, mode, out);
-  if (st != TMCS_OK) return st;
-  DecodeDevice::Sched* q = nullptr;
-  for (auto& x : d->scheds)
-    if (x.P == P && x.mode == mode) q = &x;
-  if (!q) return fail(TMCS_EDEVICE, "BP schedule cache");
-  if (q->pcL) { *out = *q; return TMCS_OK; }
-  if (d->init_pk.empty()) return fail(TMCS_EUNSUPPORTED, "packed BP state: a check has more than 30 edges");
-  auto assign = mode == 2 ? strided_assign : lpt_assign;
-  std::vector<int> rdeg(std::max(D.rows, 0)), cdeg(std::max(D.cols, 0));
-  for (int c = 0; c < D.rows; ++c) rdeg[c] = D.row_ptr[c + 1] - D.row_ptr[c];
-  for (int v = 0; v < D.cols; ++v) cdeg[v] = D.col_ptr[v + 1] - D.col_ptr[v];
-  std::vector<std::vector<int>> rl, cl;
-  assign(rdeg, P, &rl);
-  assign(cdeg, P, &cl);
-  size_t ri = 0, ci = 0;
-  for (int l = 0; l < P; ++l) { ri = std::max(ri, rl[l].size()); ci = std::max(ci, cl[l].size()); }
-  std::vector<int32_t> cslot(std::max(D.rows, 0), -1), corig, vmap(std::max(D.cols, 0), -1);
-  for (size_t i = 0; i < ri; ++i)
-    for (int l = 0; l < P; ++l)
-      if (i < rl[l].size()) { cslot[rl[l][i]] = (int32_t)corig.size(); corig.push_back(rl[l][i]); }
-  for (int l = 0; l < P; ++l)
-    for (size_t i = 0; i < cl[l].size(); ++i) vmap[cl[l][i]] = (int32_t)(i * P + l);
-  const int32_t Mpk = (int32_t)corig.size(), Npk = (int32_t)(ci * P);
-  if (Npk > R_IDX) return fail(TMCS_EUNSUPPORTED, "BP: too many column slots");
-  // padding steps read the spare slots (check Mpk, column Npk) and never store;
-  // the lists hold two rows of padding past their (even) length
-  std::vector<int2> pc((size_t)(q->Kc + 2) * P, make_int2(Npk, Mpk)), pv((size_t)(q->Kv + 2) * P, make_int2(Mpk, 0));
-  std::vector<int32_t> pce(pc.size(), 0), pve(pv.size(), 0);
-  for (int l = 0; l < P; ++l) {
-    size_t k = 0;
-    for (int c : rl[l])
-      for (int32_t e = D.row_ptr[c]; e < D.row_ptr[c + 1]; ++e, ++k) {
-        int32_t x = vmap[D.col_idx[e]] | pos_bits(e - D.row_ptr[c]);
-        if (e == D.row_ptr[c]) x |= R_FIRST;
-        if (e == D.row_ptr[c + 1] - 1) x |= R_LAST;
-        pc[k * P + l] = make_int2(x, cslot[c]);
-        pce[k * P + l] = e;
-      }
-    k = 0;
-    for (int v : cl[l]) {
-      const float lv = (float)std::log((1.0 - D.priors[v]) / D.priors[v]);
-      int32_t lbits;
-      std::memcpy(&lbits, &lv, 4);
-      for (int32_t j = D.col_ptr[v]; j < D.col_ptr[v + 1]; ++j, ++k) {
-        const int c = D.row_idx[j], e = D.csc_edge[j];
-        int32_t f = pos_bits(e - D.row_ptr[c]);
-        if (j == D.col_ptr[v]) f |= R_FIRST;
-        if (j == D.col_ptr[v + 1] - 1) f |= R_LAST;
-        pv[k * P + l] = make_int2(cslot[c] | f, lbits);
-        pve[k * P + l] = e;
-      }
-    }
-  }
-  std::vector<int4> pinit(std::max<int32_t>(Mpk, 1));
-  for (int32_t c = 0; c < Mpk; ++c) pinit[c] = d->init_pk[corig[c]];
-  if (corig.empty()) corig.push_back(0);
-  if (vmap.empty()) vmap.push_back(-1);
-  // (pcL last: a schedule with pcL set is complete)
-  if ((st = upload(&q->pvL, pv)) != TMCS_OK || (st = upload(&q->pceL, pce)) != TMCS_OK ||
-      (st = upload(&q->pveL, pve)) != TMCS_OK || (st = upload(&q->vmapL, vmap)) != TMCS_OK ||
-      (st = upload(&q->corigL, corig)) != TMCS_OK || (st = upload(&q->pinitL, pinit)) != TMCS_OK ||
-      (st = upload(&q->pcL, pc)) != TMCS_OK)
-    return st;
-  q->MpkL = Mpk;
-  q->NpkL = Npk;
-  *out = *q;
-  return TMCS_OK;
-}
-
 // Records of the packed-state team kernel with its state in device memory, for
 // team size P.  The checks with
 // edges are sorted by (degree, index) and cut into chunks of 64, one check per
@@ -1204,6 +1054,23 @@ tmcs_status get_psched(const Dem& D, DecodeDevice* d, int P, int mode, DecodeDev
   return TMCS_OK;
 }
 
+// Schedule of the LDS-state kernel for teams of P lanes, cached per P.
+tmcs_status get_chunk(const Dem& D, DecodeDevice* d, int P, ChunkSched* out) {
+  for (const auto& q : d->chunks)
+    if (q.P == P) { *out = q; return TMCS_OK; }
+  ChunkSched q;
+  tmcs_status st = build_chunk_sched(D, P, &q);
+  if (st != TMCS_OK) return st;
+  d->chunks.push_back(q);
+  *out = q;
+  return TMCS_OK;
+}
+
+// Teams of P lanes that one compute unit holds with lds bytes of dynamic LDS each.
+int chunk_teams(size_t lds, int P) {
+  return std::max(1, std::min((int)((160 * 1024) / (lds + CHUNK_LDS_STATIC)), 32 / (P / 64)));
+}
+
 // The device state cached on the DEM handle (rebuilt when the device changes).
 tmcs_status ensure_device(const Dem& dc, DecodeDevice** out) {
   Dem& D = const_cast<Dem&>(dc);
@@ -1226,39 +1093,16 @@ int device_cus() {
   return cus > 0 ? cus : 256;
 }
 
-
-// Dynamic LDS beyond 64 KB for every LDS-state variant of k_bp.
-bool bp_lds_allow(size_t lds) {
-  const void* f[] = {(const void*)k_bp<false, false, false, false>, (const void*)k_bp<true, false, false, false>,
-                     (const void*)k_bp<false, false, true, false>,  (const void*)k_bp<true, false, true, false>,
-                     (const void*)k_bp<false, false, false, true>,  (const void*)k_bp<true, false, false, true>,
-                     (const void*)k_bp<false, false, true, true>,   (const void*)k_bp<true, false, true, true>};
-  for (const void* p : f)
-    if (hipFuncSetAttribute(p, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return false;
-  return true;
-}
-
-// Launch of the team kernel variant (state in LDS: "k_bp", in device memory: "k_bp_dev").
+// Launch of the team kernel variant ("k_bp_dev": state in device memory).
 template <bool MULTI>
-void launch_k_bp(bool weighted, bool gstate, bool pk, int grid, int P, size_t lds, hipStream_t stream,
-                 const BPArgs& a, const BPMulti& mu) {
+void launch_k_bp(bool weighted, bool pk, int grid, int P, hipStream_t stream, const BPArgs& a, const BPMulti& mu) {
   const dim3 g((unsigned)grid), b((unsigned)P);
-  if (gstate) {
-    if (pk) {
-      if (weighted) TMCS_LAUNCH("k_bp_dev", (k_bp<true, true, MULTI, true>), g, b, 0, stream, a, mu);
-      else TMCS_LAUNCH("k_bp_dev", (k_bp<false, true, MULTI, true>), g, b, 0, stream, a, mu);
-    } else {
-      if (weighted) TMCS_LAUNCH("k_bp_dev", (k_bp<true, true, MULTI, false>), g, b, 0, stream, a, mu);
-      else TMCS_LAUNCH("k_bp_dev", (k_bp<false, true, MULTI, false>), g, b, 0, stream, a, mu);
-    }
+  if (pk) {
+    if (weighted) TMCS_LAUNCH("k_bp_dev", (k_bp<true, MULTI, true>), g, b, 0, stream, a, mu);
+    else TMCS_LAUNCH("k_bp_dev", (k_bp<false, MULTI, true>), g, b, 0, stream, a, mu);
   } else {
-    if (pk) {
-      if (weighted) TMCS_LAUNCH("k_bp", (k_bp<true, false, MULTI, true>), g, b, lds, stream, a, mu);
-      else TMCS_LAUNCH("k_bp", (k_bp<false, false, MULTI, true>), g, b, lds, stream, a, mu);
-    } else {
-      if (weighted) TMCS_LAUNCH("k_bp", (k_bp<true, false, MULTI, false>), g, b, lds, stream, a, mu);
-      else TMCS_LAUNCH("k_bp", (k_bp<false, false, MULTI, false>), g, b, lds, stream, a, mu);
-    }
+    if (weighted) TMCS_LAUNCH("k_bp_dev", (k_bp<true, MULTI, false>), g, b, 0, stream, a, mu);
+    else TMCS_LAUNCH("k_bp_dev", (k_bp<false, MULTI, false>), g, b, 0, stream, a, mu);
   }
 }
 
@@ -1281,6 +1125,8 @@ struct DecodePass {
   int P = 0, bp_grid_max = 0;
   size_t bp_lds = 0, team_bytes = 0;
   DecodeDevice::Sched sch;
+  bool inlds = false;          // state in LDS (bp_chunk.hip)
+  ChunkSched cs;
   bool osd_win = false, osd_pfx = false, osd_bl = false;
   bool win2 = false;           // windowed: a smaller first window, then the full one on what it leaves open
   int npad = 0, pfx_keys = 0, pfx_rank = 0, osd_grid = 0, pfx_grid = 0, win1_grid = 0, win1_rows = 0;
@@ -1337,73 +1183,77 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
   if (osd_win && cfg.osd_order > 0)
     return fail(TMCS_EUNSUPPORTED, "OSD-CS needs the dense elimination (<= 2048 detectors, <= 16384 columns)");
   const int cus = device_cus();
-  // BP launch shape: one team (workgroup) per shot in flight, state in LDS
-  // (the packed check state needs no sign bytes, and its column slots are
-  // about n: the exact size follows from the schedule; the other kernels keep the sign bytes)
-  const bool pk_ok = !d->init_pk.empty() && cfg.bp_global_state <= 1;
-  size_t bp_lds = (size_t)(D.rows + 1) * 16 + (size_t)D.cols * 4 + (pk_ok ? 0 : (size_t)d->E4 + 4);
-  bool gstate = cfg.bp_global_state != 0 || bp_lds > 160 * 1024;
-  // state in device memory: one team per shot, or on request 64 shots per
-  // workgroup in the lanes of its waves (on the surface-code NL-CNOT at d = 15..29
-  // that layout measured 2-5x slower than the team kernel)
-  const bool lanes = gstate && cfg.bp_global_state == 2 && D.rows > 0 && D.edges > 0;
-  ps.lanes = lanes;
-  if (lanes) {
+  // state in LDS wherever it fits
+  int chunk_P = -1;
+  if (cfg.bp_global_state == 0) {
+    if (d->chunk_P == 0) {
+      // up to 28 waves per CU: the passes wait on LDS and on their records, and
+      // more waves overlap more; one or two teams take all 16 each.  Measured
+      // (waves: ms): d = 5, 15 teams per CU, 1: 6.30, 2: 5.58, 3: 5.87 per 10^6
+      // shots; BB [[144,12,12]] memory, 2 teams, 8: 19.4, 12: 17.2, 16: 17.1 per
+      // 65,536; d = 11, 1 team, 12: 0.44, 16: 0.40 per 1021
+      size_t lds = 0;
+      d->chunk_P = -1;
+      if (chunk_fits(D, 512, &lds)) {
+        const int teams = chunk_teams(lds, 64);
+        d->chunk_P = 64 * (teams <= 2 ? 16 : std::max(1, std::min(16, 28 / teams)));
+      }
+    }
+    chunk_P = d->chunk_P;
+    if (chunk_P > 0 && cfg.bp_threads > 0) chunk_P = std::min(1024, std::max(64, (cfg.bp_threads + 63) / 64 * 64));
+    if (chunk_P > 0) {
+      if ((st = get_chunk(D, d, chunk_P, &ps.cs)) != TMCS_OK) return st;
+      if (ps.cs.lds() + CHUNK_LDS_STATIC > 160 * 1024) chunk_P = -1;
+    }
+  }
+  ps.inlds = chunk_P > 0;
+  // State in device memory: one team (workgroup) per shot, or on request 64
+  // shots per workgroup in the lanes of its waves (on the surface-code NL-CNOT at
+  // d = 15..29 that layout measured 2-5x slower than the team kernel), or one
+  // pass per iteration.
+  ps.gstate = !ps.inlds;
+  ps.lanes = ps.gstate && cfg.bp_global_state == 2 && D.rows > 0 && D.edges > 0;
+  ps.fused = ps.gstate && !ps.lanes && cfg.bp_global_state == 3 && D.rows > 0;
+  int per_cu = 1;
+  if (ps.lanes) {
     const int mode = cfg.bp_sched > 0 ? cfg.bp_sched : 2;
     if ((st = get_sched(D, d, LANES_WAVES, mode, &ps.sch)) != TMCS_OK) return st;
-    ps.gstate = true;
     ps.P = 64 * LANES_WAVES;
     ps.team_bytes = lanes_slab_bytes(D.rows, D.cols, d->E4);
     ps.bp_grid_max = cus * std::max(1, std::min(cfg.bp_per_cu > 0 ? cfg.bp_per_cu : 1, 2));
-  }
-  // (or one pass per iteration, on request)
-  const bool fused = gstate && !lanes && cfg.bp_global_state == 3 && D.rows > 0;
-  ps.fused = fused;
-  size_t team_bytes = fused ? fused_team_bytes(D.rows, D.cols, d->E4) : (bp_lds + 255) & ~(size_t)255;
-  // teams per CU: as many as fit in LDS; with the state in device memory, one
-  // team of 16 waves (fewer slabs in flight: at d = 15..29 that was 1.2-1.7x
-  // faster than 4 teams of 8 waves), unless the caller asks for another shape
-  int team_fit = gstate ? (cfg.bp_per_cu > 0 ? 32 : 1) : std::max(1, (int)((160 * 1024) / (bp_lds + 1024)));
-  int P = 64;
-  if (lanes) {
-  } else if (cfg.bp_threads > 0) {
-    P = cfg.bp_threads;
-  } else {
-    // about 24 waves per CU (the passes are latency-bound: more waves, more
-    // overlap), but no lane should carry much more than its share of edges
-    int G = gstate ? 16 : std::max(1, std::min(16, (24 + team_fit - 1) / team_fit));
-    P = 64 * G;
-    const int64_t cap = std::max<int64_t>(64, (2 * D.edges / std::max(d->max_row_deg, 1)) / 64 * 64);
-    while (P > 64 && P > cap) P -= 64;
-  }
-  P = std::min(1024, std::max(64, (P + 63) / 64 * 64));
-  const int sched_mode = cfg.bp_sched > 0 ? cfg.bp_sched : 1;
-  const bool pk = pk_ok && !lanes && !fused;
-  if (!lanes && (st = (fused ? get_fsched : pk ? (gstate ? get_psched : get_psched_lds) : get_sched)(
-                     D, d, P, sched_mode, &ps.sch)) != TMCS_OK)
-    return st;
-  if (pk) {
-    if (!gstate) {
-      bp_lds = (size_t)(ps.sch.MpkL + 1) * 16 + (size_t)(ps.sch.NpkL + 1) * 4;
-      if (bp_lds > 160 * 1024) {                       // (the column slots' padding tipped it over)
-        gstate = true;
-        if ((st = get_psched(D, d, P, sched_mode, &ps.sch)) != TMCS_OK) return st;
-      }
+  } else if (ps.gstate) {
+    // one team of 16 waves per CU (fewer slabs in flight: at d = 15..29 that was
+    // 1.2-1.7x faster than 4 teams of 8 waves), unless the caller asks for another
+    // shape; but no lane should carry much more than its share of edges
+    int P = cfg.bp_threads;
+    if (P <= 0) {
+      P = 1024;
+      const int64_t cap = std::max<int64_t>(64, (2 * D.edges / std::max(d->max_row_deg, 1)) / 64 * 64);
+      while (P > 64 && P > cap) P -= 64;
     }
-    // device memory: check slots (plus padding and sink), column slots (plus the +BIG slot)
-    if (gstate) bp_lds = (size_t)(ps.sch.Mpk4 + 2) * 16 + (size_t)(ps.sch.Npk + 1) * 4;
-    team_bytes = (bp_lds + 255) & ~(size_t)255;
-    team_fit = gstate ? (cfg.bp_per_cu > 0 ? 32 : 1) : std::max(1, (int)((160 * 1024) / (bp_lds + 1024)));
-  }
-  if (!gstate && bp_lds > 64 * 1024 && !bp_lds_allow(bp_lds)) return fail(TMCS_EUNSUPPORTED, "BP state does not fit in LDS");
-  const int per_cu = std::max(1, std::min({team_fit, 32 / (P / 64), cfg.bp_per_cu > 0 ? cfg.bp_per_cu : 32}));
-  ps.gstate = gstate;
-  ps.pk = pk;
-  ps.bp_lds = bp_lds;
-  if (!lanes) {
+    P = std::min(1024, std::max(64, (P + 63) / 64 * 64));
+    const int sched_mode = cfg.bp_sched > 0 ? cfg.bp_sched : 1;
+    // (the packed check state needs no sign bytes)
+    ps.pk = !ps.fused && !d->init_pk.empty();
+    if ((st = (ps.fused ? get_fsched : ps.pk ? get_psched : get_sched)(D, d, P, sched_mode, &ps.sch)) != TMCS_OK)
+      return st;
+    // check slots (plus padding and sink), column slots (plus the +BIG slot)
+    const size_t bytes = ps.fused ? fused_team_bytes(D.rows, D.cols, d->E4)
+                         : ps.pk  ? (size_t)(ps.sch.Mpk4 + 2) * 16 + (size_t)(ps.sch.Npk + 1) * 4
+                                  : (size_t)(D.rows + 1) * 16 + (size_t)D.cols * 4 + (size_t)d->E4 + 4;
+    per_cu = std::max(1, cfg.bp_per_cu > 0 ? std::min(cfg.bp_per_cu, 32 / (P / 64)) : 1);
     ps.P = P;
-    ps.team_bytes = team_bytes;
+    ps.team_bytes = (bytes + 255) & ~(size_t)255;
     ps.bp_grid_max = cus * per_cu;
+  }
+  if (ps.inlds) {
+    ps.P = chunk_P;
+    ps.bp_lds = ps.cs.lds();
+    const int fit = chunk_teams(ps.bp_lds, chunk_P);
+    ps.bp_grid_max = cus * (cfg.bp_per_cu > 0 ? std::min(fit, cfg.bp_per_cu) : fit);
+    if (cfg.weights_dev &&
+        (st = grow(&d->cw, &d->cap_cw, ((size_t)std::max(cfg.max_iter, 1) * (ps.cs.vrows + ps.cs.crows) + CHUNK_PAD_ROWS) * 64)) != TMCS_OK)
+      return st;
   }
   // shots per internal pass: as few passes as the OSD LLR staging allows
   // (<= 8 GiB), each ending on its slowest teams; passes of equal size
@@ -1477,9 +1327,9 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
   ps.win1_grid = win1_grid; ps.win1_lds = win1_lds; ps.win1_rows = win1_rows; ps.win1_mw = mw1;
   if ((st = grow(&d->queue, &d->cap_queue, (size_t)chunk)) != TMCS_OK) return st;
   if ((st = grow(&d->synd, &d->cap_synd, (size_t)chunk * (size_t)std::max(mw, 1))) != TMCS_OK) return st;
-  if (gstate && !lanes && (st = grow(&d->gstate, &d->cap_gstate, (size_t)cus * per_cu * team_bytes)) != TMCS_OK)
+  if (ps.gstate && !ps.lanes && (st = grow(&d->gstate, &d->cap_gstate, (size_t)cus * per_cu * ps.team_bytes)) != TMCS_OK)
     return st;
-  if (lanes && !shared_slab &&
+  if (ps.lanes && !shared_slab &&
       (st = grow(&d->gstate, &d->cap_gstate, (size_t)lanes_grid(ps.bp_grid_max, ps.team_bytes, chunk) * ps.team_bytes)) !=
           TMCS_OK)
     return st;
@@ -1508,22 +1358,14 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
 }
 
 // BP kernel arguments of the chunk [s0, s0 + ns) of a pass.
-BPArgs bp_args(const DecodePass& ps, const uint64_t* det_unused, uint64_t* pred, tmcs_decode_stats* stats,
-               int64_t s0, int64_t ns) {
-  (void)det_unused;
+BPArgs bp_args(const DecodePass& ps, uint64_t* pred, tmcs_decode_stats* stats, int64_t s0, int64_t ns) {
   const DecodeDevice* d = ps.d;
   const Dem& D = *ps.D;
   const tmcs_decoder_cfg& cfg = ps.cfg;
   BPArgs a;
   a.csched = ps.sch.c; a.vsched = ps.sch.v; a.Kc = ps.sch.Kc; a.Kv = ps.sch.Kv; a.init = d->init; a.sign0 = d->sign0;
-  if (ps.gstate) {
-    a.pce = ps.sch.pce; a.pve = ps.sch.pve; a.vmap = ps.sch.vmap;
-    a.corig = ps.sch.corig4; a.pinit = ps.sch.pinit4; a.Mpk = ps.sch.Mpk4; a.Npk = ps.sch.Npk;
-  } else {
-    a.pce = ps.sch.pceL; a.pve = ps.sch.pveL; a.vmap = ps.sch.vmapL;
-    a.corig = ps.sch.corigL; a.pinit = ps.sch.pinitL; a.Mpk = ps.sch.MpkL; a.Npk = ps.sch.NpkL;
-  }
-  a.pcs = ps.sch.pcL; a.pvs = ps.sch.pvL;
+  a.pce = ps.sch.pce; a.pve = ps.sch.pve; a.vmap = ps.sch.vmap;
+  a.corig = ps.sch.corig4; a.pinit = ps.sch.pinit4; a.Mpk = ps.sch.Mpk4; a.Npk = ps.sch.Npk;
   a.pcs4 = ps.sch.pc4; a.pvs4 = ps.sch.pv4; a.lamp = ps.sch.lamp;
   a.Kc4 = ps.sch.Kc4; a.Kv4 = ps.sch.Kv4;
   a.lam = d->lam; a.obs_mask = d->obs_mask; a.ow = D.obs_words;
@@ -1540,6 +1382,46 @@ BPArgs bp_args(const DecodePass& ps, const uint64_t* det_unused, uint64_t* pred,
   a.fsched = ps.sch.f; a.Kf = ps.sch.Kf; a.csc_row = d->csc_row; a.csc_edge = d->csc_edge;
   for (int w = 0; w < MAX_OW; ++w) a.pm_iso[w] = d->pm_iso[w];
   return a;
+}
+
+// The same for the LDS-state kernel.
+ChunkArgs chunk_args(const DecodePass& ps, uint64_t* pred, tmcs_decode_stats* stats, int64_t s0, int64_t ns) {
+  const DecodeDevice* d = ps.d;
+  const Dem& D = *ps.D;
+  const tmcs_decoder_cfg& cfg = ps.cfg;
+  const ChunkSched& c = ps.cs;
+  ChunkArgs a;
+  a.vrec = c.vrec; a.crec = c.crec; a.tab = c.tab; a.lamp = c.lamp; a.pinit = c.pinit; a.vmap = c.vmap;
+  a.oslot = c.oslot; a.omask = c.omask;
+  a.Ms = c.Ms; a.Ns = c.Ns; a.ntab = c.ntab; a.noc = c.noc;
+  a.n = D.cols; a.ow = D.obs_words; a.mw = std::max(ps.mw, 1); a.T = cfg.max_iter; a.alpha = cfg.alpha;
+  a.wv_stride = (int64_t)c.vrows * 64; a.wc_stride = (int64_t)c.crows * 64;
+  a.wv = cfg.weights_dev ? d->cw : nullptr;
+  a.wc = cfg.weights_dev ? d->cw + a.wv_stride * std::max(cfg.max_iter, 1) : nullptr;
+  a.lam = d->lam; a.synd = d->synd; a.lone = d->lone; a.stride = ps.stride; a.shot0 = s0; a.nshots = ns;
+  a.queue = ps.full ? nullptr : d->queue;
+  a.counters = d->counters; a.osd_queue = d->osd_queue; a.osd_llr = d->osd_llr; a.pred = pred; a.stats = stats;
+  a.ehat = cfg.ehat_dev; a.llr = cfg.llr_dev; a.iters = cfg.iters_dev; a.flags = cfg.flags_dev;
+  a.use_osd = cfg.use_osd; a.nobs = D.nobs;
+  for (int w = 0; w < MAX_OW; ++w) { a.pm_lam[w] = d->pm_lam[w]; a.pm_iso[w] = d->pm_iso[w]; }
+  return a;
+}
+
+// Messages by plain comparisons: per-edge weights, or values that could reach
+// infinity.  |q| at most grows by 1 + (dv + 1) |alpha| per iteration (dv: the
+// largest column degree), from the largest |lambda|, or from the 1e30 of an
+// empty minimum where a check has one edge.
+bool chunk_exact(const DecodePass& ps) {
+  if (ps.cfg.weights_dev) return true;
+  const double grow = std::log10(1.0 + (ps.D->max_col_deg + 1.0) * std::fabs((double)ps.cfg.alpha));
+  return !(ps.d->log_start + grow * (ps.cfg.max_iter + 1.0) < 37.0);
+}
+
+// The weights of a weighted item, laid out for its schedule.
+tmcs_status chunk_weights(const DecodePass& ps, hipStream_t stream) {
+  if (!ps.inlds || !ps.cfg.weights_dev) return TMCS_OK;
+  return launch_chunk_weights(ps.cs, ps.cfg.weights_dev, ps.cfg.max_iter, ps.D->edges, ps.d->cw,
+                              ps.d->cw + (int64_t)ps.cs.vrows * 64 * std::max(ps.cfg.max_iter, 1), stream);
 }
 
 // OSD kernel arguments of the chunk starting at s0.
@@ -1599,15 +1481,19 @@ void decode_stage(const DecodePass& ps, const uint64_t* det, tmcs_decode_stats* 
   }
 }
 
-tmcs_status decode_bp_launch(const DecodePass& ps, const BPArgs& a, int64_t ns, hipStream_t stream) {
+tmcs_status decode_bp_launch(const DecodePass& ps, uint64_t* pred, tmcs_decode_stats* stats, int64_t s0, int64_t ns,
+                             hipStream_t stream) {
   const int bp_grid = (int)std::min<int64_t>((int64_t)ps.bp_grid_max, std::max<int64_t>(ns, 1));
+  if (ps.inlds)
+    return launch_bp_chunk(chunk_args(ps, pred, stats, s0, ns), ChunkMulti{nullptr, 0, nullptr}, chunk_exact(ps),
+                           ps.cs.wide, bp_grid, ps.P, ps.bp_lds, stream);
+  const BPArgs a = bp_args(ps, pred, stats, s0, ns);
   const BPMulti none{nullptr, 0, nullptr};
   if (ps.lanes)
     return launch_bp_lanes(a, none, ps.cfg.weights_dev != nullptr, lanes_grid(ps.bp_grid_max, ps.team_bytes, ns),
                            stream);
   if (ps.fused) return launch_bp_fused(a, none, ps.cfg.weights_dev != nullptr, bp_grid, ps.P, stream);
-  launch_k_bp<false>(ps.cfg.weights_dev != nullptr, ps.gstate, ps.pk, bp_grid, ps.P, ps.gstate ? 0 : ps.bp_lds, stream,
-                     a, none);
+  launch_k_bp<false>(ps.cfg.weights_dev != nullptr, ps.pk, bp_grid, ps.P, stream, a, none);
   return hip_check(hipGetLastError(), "k_bp launch");
 }
 
@@ -1653,10 +1539,11 @@ tmcs_status decode_run(const Dem& D, const tmcs_decoder_cfg& cfg, const uint64_t
   tmcs_status st = decode_prepare(D, cfg, n_shots, state, stream, &ps);
   if (st != TMCS_OK) return st;
   decode_zero_pred(ps, pred, stream);
+  if ((st = chunk_weights(ps, stream)) != TMCS_OK) return st;
   for (int64_t s0 = 0; s0 < (int64_t)n_shots; s0 += ps.chunk) {
     const int64_t ns = std::min<int64_t>(ps.chunk, (int64_t)n_shots - s0);
     decode_stage(ps, det, stats, s0, ns, stream);
-    if ((st = decode_bp_launch(ps, bp_args(ps, det, pred, stats, s0, ns), ns, stream)) != TMCS_OK) return st;
+    if ((st = decode_bp_launch(ps, pred, stats, s0, ns, stream)) != TMCS_OK) return st;
     if ((st = decode_osd_launch(ps, pred, stats, s0, stream)) != TMCS_OK) return st;
   }
   return TMCS_OK;
@@ -1677,6 +1564,9 @@ struct MultiDecode {
   };
   struct BPGroup {
     bool gstate = false, lanes = false, fused = false, pk = false, weighted = false;
+    bool inlds = false, wide = false, exact = false;
+    ChunkArgs* ctab = nullptr;       // inlds: device [items]
+    ChunkArgs cfirst{};
     unsigned char* slab = nullptr;   // lanes: the state of every workgroup, shared by the group's items
     int P = 0, grid = 0;
     size_t lds = 0;
@@ -1707,7 +1597,7 @@ struct MultiDecode {
 
 void decode_multi_free(MultiDecode* m) {
   if (!m) return;
-  for (auto& g : m->bp) { hipFree(g.tab); hipFree(g.slab); }
+  for (auto& g : m->bp) { hipFree(g.tab); hipFree(g.ctab); hipFree(g.slab); }
   hipFree(m->osd_tab);
   hipFree(m->osd_tab2);
   hipFree(m->next);
@@ -1738,7 +1628,8 @@ tmcs_status decode_multi_create(const std::vector<MultiItemSpec>& specs, uint64_
     const DecodePass& ps = m->items[i].ps;
     MultiDecode::BPGroup* g = nullptr;
     for (auto& q : m->bp)
-      if (q.gstate == ps.gstate && q.lanes == ps.lanes && q.fused == ps.fused && q.pk == ps.pk && q.P == ps.P) g = &q;
+      if (q.gstate == ps.gstate && q.lanes == ps.lanes && q.fused == ps.fused && q.pk == ps.pk && q.P == ps.P &&
+          q.inlds == ps.inlds && (!ps.inlds || q.wide == ps.cs.wide)) g = &q;
     if (!g) {
       m->bp.push_back(MultiDecode::BPGroup());
       g = &m->bp.back();
@@ -1746,13 +1637,16 @@ tmcs_status decode_multi_create(const std::vector<MultiItemSpec>& specs, uint64_
       g->lanes = ps.lanes;
       g->fused = ps.fused;
       g->pk = ps.pk;
+      g->inlds = ps.inlds;
+      g->wide = ps.inlds && ps.cs.wide;
       g->P = ps.P;
       g->grid = ps.bp_grid_max;
     }
     g->items.push_back(i);
     g->weighted = g->weighted || ps.cfg.weights_dev != nullptr;
+    g->exact = g->exact || chunk_exact(ps);
     g->grid = std::min(g->grid, ps.bp_grid_max);
-    if (!ps.gstate) g->lds = std::max(g->lds, ps.bp_lds);
+    if (ps.inlds) g->lds = std::max(g->lds, ps.bp_lds);
   }
   // Heaviest items first in every group (workgroups take the items in order):
   // the launch then ends on the cheapest shots instead of waiting for the last
@@ -1769,14 +1663,16 @@ tmcs_status decode_multi_create(const std::vector<MultiItemSpec>& specs, uint64_
   }
   const int cus = device_cus();
   for (auto& g : m->bp) {
-    if (!g.gstate) {
-      // teams resident per CU with the largest state of the group
-      const int fit = std::max(1, std::min((int)((160 * 1024) / (g.lds + 1024)), 32 / (g.P / 64)));
-      g.grid = std::min(g.grid, cus * fit);
-      if (g.lds > 64 * 1024 && !bp_lds_allow(g.lds)) {
-        decode_multi_free(m);
-        return fail(TMCS_EUNSUPPORTED, "BP state does not fit in LDS");
+    if (g.inlds) {
+      g.grid = std::min(g.grid, cus * chunk_teams(g.lds, g.P));
+      std::vector<ChunkArgs> tab;
+      for (int i : g.items) {
+        const auto& it = m->items[i];
+        tab.push_back(chunk_args(it.ps, it.pred, it.stats, 0, (int64_t)batch));
       }
+      g.cfirst = tab[0];
+      if ((st = upload(&g.ctab, tab)) != TMCS_OK) { decode_multi_free(m); return st; }
+      continue;
     }
     if (g.lanes) {
       // one state slab per workgroup sized for the largest item
@@ -1792,7 +1688,7 @@ tmcs_status decode_multi_create(const std::vector<MultiItemSpec>& specs, uint64_
     std::vector<BPArgs> tab;
     for (int i : g.items) {
       const auto& it = m->items[i];
-      tab.push_back(bp_args(it.ps, it.det, it.pred, it.stats, 0, (int64_t)batch));
+      tab.push_back(bp_args(it.ps, it.pred, it.stats, 0, (int64_t)batch));
       if (g.lanes) {
         tab.back().gstate = g.slab;
         tab.back().team_bytes = g.lds;
@@ -1865,11 +1761,18 @@ tmcs_status decode_multi_enqueue(MultiDecode* m, hipStream_t stream) {
   }
   TMCS_LAUNCH("k_zero_i32", k_zero_i32, dim3(1), dim3(64), 0, stream, m->next, 3);
   tmcs_status st;
+  for (auto& it : m->items)
+    if ((st = chunk_weights(it.ps, stream)) != TMCS_OK) return st;
   for (auto& g : m->bp) {
     // (the BP job counter is shared by the groups in turn: zeroed before each)
     if (&g != &m->bp.front()) TMCS_LAUNCH("k_zero_i32", k_zero_i32, dim3(1), dim3(64), 0, stream, m->next, 1);
     const BPMulti mu{g.tab, (int32_t)g.items.size(), m->next};
     const int grid = std::max(1, g.grid);
+    if (g.inlds) {
+      const ChunkMulti cmu{g.ctab, (int32_t)g.items.size(), m->next};
+      if ((st = launch_bp_chunk(g.cfirst, cmu, g.exact, g.wide, grid, g.P, g.lds, stream)) != TMCS_OK) return st;
+      continue;
+    }
     const BPArgs& a0 = g.first;
     if (g.lanes) {
       if ((st = launch_bp_lanes(a0, mu, g.weighted, grid, stream)) != TMCS_OK) return st;
@@ -1879,7 +1782,7 @@ tmcs_status decode_multi_enqueue(MultiDecode* m, hipStream_t stream) {
       if ((st = launch_bp_fused(a0, mu, g.weighted, grid, g.P, stream)) != TMCS_OK) return st;
       continue;
     }
-    launch_k_bp<true>(g.weighted, g.gstate, g.pk, grid, g.P, g.gstate ? 0 : g.lds, stream, a0, mu);
+    launch_k_bp<true>(g.weighted, g.pk, grid, g.P, stream, a0, mu);
     if ((st = hip_check(hipGetLastError(), "k_bp launch")) != TMCS_OK) return st;
   }
   // Items outside the windowed launch (another window shape, or no window) take

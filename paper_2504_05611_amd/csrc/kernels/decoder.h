@@ -167,16 +167,12 @@ struct BPArgs {
   const int32_t* csc_row;    // [E] check of each CSC entry (columns of degree >= 3)
   const int32_t* csc_edge;   // [E] CSR edge of each CSC entry
   uint64_t pm_iso[MAX_OW];   // observables of the columns without edges whose lambda < 0
-  // packed-state team kernel.  State in device memory: 4-byte records over
-  // degree chunks, lane l's k-th check at slot c' = k P + l and its k-th column
-  // at v' = k P + l.  State in LDS: int2 records over longest-processing-time
-  // lists, checks numbered in the order the lanes first reach them.
-  const int2* pcs;           // LDS: [Kc + 2][P] check pass {v' | position | flags, c'}
-  const int2* pvs;           // LDS: [Kv + 2][P] variable pass {c' | position | flags, lambda_v bits}
+  // packed-state team kernel: 4-byte records over degree chunks, lane l's k-th
+  // check at slot c' = k P + l and its k-th column at v' = k P + l
   const int32_t* pce;        // CSR edge of each check-pass record (per-edge weights), laid out as its records
   const int32_t* pve;        // the same for the variable pass
   const int32_t* vmap;       // [n] v -> v' (-1: a column without edges)
-  const int32_t* corig;      // c' -> c; device memory: [Mpk + 2] (-1: an empty slot, the padding slot Mpk, the sink Mpk + 1)
+  const int32_t* corig;      // [Mpk + 2] c' -> c (-1: an empty slot, the padding slot Mpk, the sink Mpk + 1)
   const int4* pinit;         // packed check state of iteration 1 by slot (s_c = 0; argmin as 2 + position)
   int32_t Mpk, Npk;          // check slots, column slots
   const int32_t* pcs4;       // [Kc4 + BP_AHEAD][P] check pass: v' | position | flags
