@@ -6,7 +6,7 @@
 // edge as possible: everything that only steers a loop is the same in the 64
 // lanes of a wave and lives in scalar registers.
 //
-// Checks are cut into parts of at most CHUNK_MAX_DEG edges, f = 1, 2, 4, ... equal
+// Checks are cut into parts of at most PART_MAX_DEG edges, f = 1, 2, 4, ... equal
 // parts to a check, in f neighbouring lanes.  64 parts with the same f and nearly
 // the same number of edges form a chunk, one part per lane; 64 columns of nearly
 // the same degree form a column chunk.  A chunk takes as many steps as its largest
@@ -52,22 +52,16 @@
 #include "../host/device.h"
 #include "../host/timing.h"
 #include "bp_chunk.h"
+#include "bp_team.h"
 
 namespace tmcs {
 namespace dec {
 
 namespace {
 
-constexpr int CHUNK_MAX_DEG = 26;           // sign bits 31..6 of the word
-constexpr uint32_t W_SIGNS = 0xFFFFFFC0u;
-constexpr uint32_t W_SC = 0x20u;
-constexpr uint32_t W_POS = 0x1Fu;
 constexpr int MAX_RUNS = 24;                // runs per wave and pass that the LDS estimate allows for
 constexpr int R_PART = 12;                   // column-pass record: part address << R_PART | j
 constexpr int HDR = 8;                      // table words per wave before the runs
-
-__device__ __forceinline__ uint32_t gload(const uint32_t* p) { return *(const TMCS_GLOBAL_AS uint32_t*)p; }
-using dec::gload;
 
 // Value of the lane whose index differs in bit `step`, for values that agree
 // within groups of `step` lanes (1, 2: swaps; 4, 8: mirrors of 8 and 16 lanes).
@@ -83,25 +77,7 @@ __device__ __forceinline__ T part_xchg(T x, int step) {
   return __builtin_bit_cast(T, r);
 }
 
-__device__ __forceinline__ float with_sign(float mag, uint32_t s) {
-  return __uint_as_float(__float_as_uint(mag) ^ (s & 0x80000000u));
-}
-
-// The launch's arguments (kernel arguments, or an item's entry of a multi
-// launch's table), read through the scalar cache where they are used: held in
-// registers all at once they would not fit beside the passes' own scalars.
-#define TMCS_CONST_AS __attribute__((address_space(4)))
 using ArgsPtr = const TMCS_CONST_AS ChunkArgs*;
-// The same pointer, opaque to the compiler, so that what is read through it is
-// read here and not at the start of the kernel.
-__device__ __forceinline__ ArgsPtr reread(ArgsPtr p) {
-  asm volatile("" : "+s"(p));
-  return p;
-}
-template <typename T>
-__device__ __forceinline__ T at_byte(const T* base, uint32_t byte) {
-  return gload((const T*)((const char*)base + byte));
-}
 
 template <bool EXACT, bool MULTI, bool WIDE>
 __global__ void __launch_bounds__(1024, 8) k_bp_chunk(ChunkArgs, ChunkMulti mu) {
@@ -359,7 +335,7 @@ __global__ void __launch_bounds__(1024, 8) k_bp_chunk(ChunkArgs, ChunkMulti mu) 
               part(slot12, &n1o, &n2o, &wo);
               const uint32_t ago = wo & W_POS;
               float n1 = BP_BIG, n2 = BP_BIG;
-              uint32_t ag = W_POS, nb = 0u, hx = 0u;
+              uint32_t lt = 0u, nb = 0u, hx = 0u;    // lt: steps that brought a new minimum, the last in bit 0
               auto step = [&](int j, float Lv, float wt) {
                 if constexpr (EXACT) hx ^= Lv < 0.0f ? 0x80000000u : 0u;
                 else hx ^= __float_as_uint(Lv);
@@ -368,17 +344,19 @@ __global__ void __launch_bounds__(1024, 8) k_bp_chunk(ChunkArgs, ChunkMulti mu) 
                   if (EXACT && use_w) mag = __fmul_rn(wt, mag);
                   const float qv = __fsub_rn(Lv, with_sign(mag, wo << j));
                   const float aq = fabsf(qv);
-                  const bool lt1 = aq < n1;
                   if constexpr (EXACT) {
+                    const bool lt1 = aq < n1;
                     n2 = lt1 ? n1 : (aq < n2 ? aq : n2);
                     n1 = lt1 ? aq : n1;
+                    lt = (lt << 1) | (lt1 ? 1u : 0u);
                     nb = (nb << 1) | (qv < 0.0f ? 1u : 0u);
                   } else {
+                    // (a difference of floats is negative exactly when the first is smaller)
+                    lt = __builtin_amdgcn_alignbit(lt, __float_as_uint(__fsub_rn(aq, n1)), 31);
                     n2 = __builtin_amdgcn_fmed3f(n1, n2, aq);
-                    n1 = lt1 ? aq : n1;
+                    n1 = __builtin_amdgcn_fmed3f(n1, aq, -__builtin_inff());   // (min, without a canonicalising move)
                     nb = __builtin_amdgcn_alignbit(nb, __float_as_uint(qv), 31);
                   }
-                  ag = lt1 ? (uint32_t)j : ag;
                 }
               };
 #pragma unroll 2
@@ -417,7 +395,8 @@ __global__ void __launch_bounds__(1024, 8) k_bp_chunk(ChunkArgs, ChunkMulti mu) 
               const uint32_t sc = wo & W_SC;
               unsat |= (int)((hx >> 31) ^ (sc >> 5));
               if constexpr (update) {
-                if (n1 != m1) ag = W_POS;          // the minimum is another part's
+                // (lt = 0, or a minimum that is another part's: none here)
+                const uint32_t ag = lt && n1 == m1 ? (uint32_t)(K - __ffs(lt)) : W_POS;
                 // message sign of edge j = s_c + parity + sgn q_j (mod 2)
                 const uint32_t flip = (par >> 31) != (sc >> 5) ? W_SIGNS : 0u;
                 float* p = (float*)(st + slot12);
@@ -587,7 +566,7 @@ bool check_chunks(const Dem& D, int most, std::vector<Chunk>* out) {
 // The part size whose chunks take the team the fewest instructions, with a state of at most max_parts parts.
 bool best_check_chunks(const Dem& D, int NW, size_t max_parts, std::vector<Chunk>* best, std::vector<std::vector<int>>* waves) {
   long best_cost = -1;
-  for (int most : {CHUNK_MAX_DEG, 20, 16, 12, 10, 8}) {
+  for (int most : {PART_MAX_DEG, 20, 16, 12, 10, 8}) {
     std::vector<Chunk> ch;
     std::vector<std::vector<int>> wv;
     if (!check_chunks(D, most, &ch) || ch.size() * 64 > max_parts) continue;

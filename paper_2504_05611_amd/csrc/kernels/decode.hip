@@ -41,6 +41,7 @@
 #include "../host/device.h"
 #include "../host/timing.h"
 #include "bp_chunk.h"
+#include "bp_stream.h"
 #include "decoder.h"
 
 namespace tmcs {
@@ -79,6 +80,8 @@ struct DecodeDevice {
   std::vector<ChunkSched> chunks;   // schedules of the LDS-state kernel, one per team size used so far
   double log_start = 30.0;          // log10 of the largest magnitude BP starts from
   int chunk_P = 0;                  // its default team size (-1: the state does not fit)
+  std::vector<StreamSched> streams; // schedules of the streaming kernel, one per team size used so far
+  std::vector<int> no_stream;       // team sizes it does not take this DEM with
   float* cw = nullptr;              // per-edge weights by schedule step
   size_t cap_cw = 0;
   // scratch
@@ -658,6 +661,7 @@ void free_device(DecodeDevice* d) {
     hipFree(q.pc4); hipFree(q.pv4); hipFree(q.corig4); hipFree(q.pinit4); hipFree(q.lamp);
   }
   for (auto& q : d->chunks) free_chunk_sched(&q);
+  for (auto& q : d->streams) free_stream_sched(&q);
   hipFree(d->cw);
   *d = DecodeDevice();
 }
@@ -1066,10 +1070,25 @@ tmcs_status get_chunk(const Dem& D, DecodeDevice* d, int P, ChunkSched* out) {
   return TMCS_OK;
 }
 
-// Teams of P lanes that one compute unit holds with lds bytes of dynamic LDS each.
-int chunk_teams(size_t lds, int P) {
-  return std::max(1, std::min((int)((160 * 1024) / (lds + CHUNK_LDS_STATIC)), 32 / (P / 64)));
+// The same for the streaming kernel; *ok: whether it takes this DEM.
+tmcs_status get_stream(const Dem& D, DecodeDevice* d, int P, bool* ok, StreamSched* out) {
+  *ok = false;
+  for (const auto& q : d->streams)
+    if (q.P == P) { *out = q; *ok = true; return TMCS_OK; }
+  for (int p : d->no_stream)
+    if (p == P) return TMCS_OK;
+  StreamSched q;
+  tmcs_status st = build_stream_sched(D, P, &q);
+  if (st == TMCS_EUNSUPPORTED) { d->no_stream.push_back(P); return TMCS_OK; }
+  if (st != TMCS_OK) return st;
+  d->streams.push_back(q);
+  *out = q;
+  *ok = true;
+  return TMCS_OK;
 }
+
+// Teams of P lanes that one compute unit holds with lds bytes of LDS each.
+int lds_teams(size_t lds, int P) { return std::max(1, std::min((int)((160 * 1024) / lds), 32 / (P / 64))); }
 
 // The device state cached on the DEM handle (rebuilt when the device changes).
 tmcs_status ensure_device(const Dem& dc, DecodeDevice** out) {
@@ -1127,12 +1146,24 @@ struct DecodePass {
   DecodeDevice::Sched sch;
   bool inlds = false;          // state in LDS (bp_chunk.hip)
   ChunkSched cs;
+  bool stream = false;         // state streamed through LDS (bp_stream.hip)
+  StreamSched ss;
   bool osd_win = false, osd_pfx = false, osd_bl = false;
   bool win2 = false;           // windowed: a smaller first window, then the full one on what it leaves open
   int npad = 0, pfx_keys = 0, pfx_rank = 0, osd_grid = 0, pfx_grid = 0, win1_grid = 0, win1_rows = 0;
   int win1_mw = 0;             // words of local rows of the first window (WIN_SMALL_MW or WIN_MID_MW)
   size_t osd_lds = 0, pfx_lds = 0, win1_lds = 0;
 };
+
+// Messages by plain comparisons: per-edge weights, or values that could reach
+// infinity.  |q| at most grows by 1 + (dv + 1) |alpha| per iteration (dv: the
+// largest column degree), from the largest |lambda|, or from the 1e30 of an
+// empty minimum where a check has one edge.
+bool bp_exact(const DecodePass& ps) {
+  if (ps.cfg.weights_dev) return true;
+  const double grow = std::log10(1.0 + (ps.D->max_col_deg + 1.0) * std::fabs((double)ps.cfg.alpha));
+  return !(ps.d->log_start + grow * (ps.cfg.max_iter + 1.0) < 37.0);
+}
 
 // Expected number of detection events per shot: sum over detectors of the
 // probability that an odd number of its mechanisms fire.
@@ -1195,7 +1226,7 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
       size_t lds = 0;
       d->chunk_P = -1;
       if (chunk_fits(D, 512, &lds)) {
-        const int teams = chunk_teams(lds, 64);
+        const int teams = lds_teams(lds + CHUNK_LDS_STATIC, 64);
         d->chunk_P = 64 * (teams <= 2 ? 16 : std::max(1, std::min(16, 28 / teams)));
       }
     }
@@ -1207,11 +1238,27 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
     }
   }
   ps.inlds = chunk_P > 0;
+  // A larger state is streamed through LDS where the DEM is graph-like; so is one
+  // that leaves room for a single team per CU, once there are shots enough to
+  // keep both teams of the streaming kernel busy (d = 11, chunks / streaming, ms:
+  // 1021 shots 0.41 / 0.47, 2048 0.64 / 0.62, 8192 2.00 / 1.80, 16,384 3.95 / 3.27;
+  // d = 13: 1021 0.72 / 0.77, 8192 3.94 / 3.58).  16 waves per team: d = 21, 4096
+  // shots, 8 / 12 / 16 waves 16.6 / 14.1 / 13.3 ms.
+  const bool one_team = ps.inlds && lds_teams(ps.cs.lds() + CHUNK_LDS_STATIC, 64) == 1;
+  if (cfg.bp_global_state == 0 && (!ps.inlds || (one_team && n_shots >= 8ull * cus)) && !bp_exact(ps)) {
+    const int P = std::min(1024, std::max(64, cfg.bp_threads > 0 ? (cfg.bp_threads + 63) / 64 * 64 : 1024));
+    if ((st = get_stream(D, d, P, &ps.stream, &ps.ss)) != TMCS_OK) return st;
+    if (ps.stream && ps.ss.lds() > 160 * 1024) ps.stream = false;
+    if (ps.stream) {
+      ps.inlds = false;
+      ps.P = P;
+    }
+  }
   // State in device memory: one team (workgroup) per shot, or on request 64
   // shots per workgroup in the lanes of its waves (on the surface-code NL-CNOT at
   // d = 15..29 that layout measured 2-5x slower than the team kernel), or one
   // pass per iteration.
-  ps.gstate = !ps.inlds;
+  ps.gstate = !ps.inlds && !ps.stream;
   ps.lanes = ps.gstate && cfg.bp_global_state == 2 && D.rows > 0 && D.edges > 0;
   ps.fused = ps.gstate && !ps.lanes && cfg.bp_global_state == 3 && D.rows > 0;
   int per_cu = 1;
@@ -1249,11 +1296,18 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
   if (ps.inlds) {
     ps.P = chunk_P;
     ps.bp_lds = ps.cs.lds();
-    const int fit = chunk_teams(ps.bp_lds, chunk_P);
+    const int fit = lds_teams(ps.bp_lds + CHUNK_LDS_STATIC, chunk_P);
     ps.bp_grid_max = cus * (cfg.bp_per_cu > 0 ? std::min(fit, cfg.bp_per_cu) : fit);
     if (cfg.weights_dev &&
         (st = grow(&d->cw, &d->cap_cw, ((size_t)std::max(cfg.max_iter, 1) * (ps.cs.vrows + ps.cs.crows) + CHUNK_PAD_ROWS) * 64)) != TMCS_OK)
       return st;
+  }
+  if (ps.stream) {
+    ps.bp_lds = ps.ss.lds();
+    ps.team_bytes = ps.ss.team_bytes();
+    const int fit = lds_teams(ps.bp_lds, ps.P);
+    per_cu = cfg.bp_per_cu > 0 ? std::min(fit, cfg.bp_per_cu) : fit;
+    ps.bp_grid_max = cus * per_cu;
   }
   // shots per internal pass: as few passes as the OSD LLR staging allows
   // (<= 8 GiB), each ending on its slowest teams; passes of equal size
@@ -1327,7 +1381,7 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
   ps.win1_grid = win1_grid; ps.win1_lds = win1_lds; ps.win1_rows = win1_rows; ps.win1_mw = mw1;
   if ((st = grow(&d->queue, &d->cap_queue, (size_t)chunk)) != TMCS_OK) return st;
   if ((st = grow(&d->synd, &d->cap_synd, (size_t)chunk * (size_t)std::max(mw, 1))) != TMCS_OK) return st;
-  if (ps.gstate && !ps.lanes && (st = grow(&d->gstate, &d->cap_gstate, (size_t)cus * per_cu * ps.team_bytes)) != TMCS_OK)
+  if ((ps.stream || (ps.gstate && !ps.lanes)) && (st = grow(&d->gstate, &d->cap_gstate, (size_t)cus * per_cu * ps.team_bytes)) != TMCS_OK)
     return st;
   if (ps.lanes && !shared_slab &&
       (st = grow(&d->gstate, &d->cap_gstate, (size_t)lanes_grid(ps.bp_grid_max, ps.team_bytes, chunk) * ps.team_bytes)) !=
@@ -1407,14 +1461,25 @@ ChunkArgs chunk_args(const DecodePass& ps, uint64_t* pred, tmcs_decode_stats* st
   return a;
 }
 
-// Messages by plain comparisons: per-edge weights, or values that could reach
-// infinity.  |q| at most grows by 1 + (dv + 1) |alpha| per iteration (dv: the
-// largest column degree), from the largest |lambda|, or from the 1e30 of an
-// empty minimum where a check has one edge.
-bool chunk_exact(const DecodePass& ps) {
-  if (ps.cfg.weights_dev) return true;
-  const double grow = std::log10(1.0 + (ps.D->max_col_deg + 1.0) * std::fabs((double)ps.cfg.alpha));
-  return !(ps.d->log_start + grow * (ps.cfg.max_iter + 1.0) < 37.0);
+// The same for the streaming kernel.
+StreamArgs stream_args(const DecodePass& ps, uint64_t* pred, tmcs_decode_stats* stats, int64_t s0, int64_t ns) {
+  const DecodeDevice* d = ps.d;
+  const Dem& D = *ps.D;
+  const tmcs_decoder_cfg& cfg = ps.cfg;
+  const StreamSched& c = ps.ss;
+  StreamArgs a;
+  a.rec = c.rec; a.desc = c.desc; a.row0 = c.row0; a.pinit = c.pinit; a.lamtab = c.lamtab; a.lrec = c.lrec; a.lamL = c.lamL;
+  a.vrec = c.vrec; a.ocol = c.ocol; a.omask = c.omask;
+  a.NT = c.NT; a.h = c.h; a.R = c.R; a.NL = c.NL; a.KL = c.KL; a.noc = c.noc;
+  a.n = D.cols; a.ow = D.obs_words; a.mw = std::max(ps.mw, 1); a.T = cfg.max_iter; a.alpha = cfg.alpha;
+  a.state = d->gstate; a.buf = (int64_t)c.buf_bytes();
+  a.lam = d->lam; a.synd = d->synd; a.lone = d->lone; a.stride = ps.stride; a.shot0 = s0; a.nshots = ns;
+  a.queue = ps.full ? nullptr : d->queue;
+  a.counters = d->counters; a.osd_queue = d->osd_queue; a.osd_llr = d->osd_llr; a.pred = pred; a.stats = stats;
+  a.ehat = cfg.ehat_dev; a.llr = cfg.llr_dev; a.iters = cfg.iters_dev; a.flags = cfg.flags_dev;
+  a.use_osd = cfg.use_osd; a.nobs = D.nobs;
+  for (int w = 0; w < MAX_OW; ++w) { a.pm_lam[w] = d->pm_lam[w]; a.pm_iso[w] = d->pm_iso[w]; }
+  return a;
 }
 
 // The weights of a weighted item, laid out for its schedule.
@@ -1485,8 +1550,11 @@ tmcs_status decode_bp_launch(const DecodePass& ps, uint64_t* pred, tmcs_decode_s
                              hipStream_t stream) {
   const int bp_grid = (int)std::min<int64_t>((int64_t)ps.bp_grid_max, std::max<int64_t>(ns, 1));
   if (ps.inlds)
-    return launch_bp_chunk(chunk_args(ps, pred, stats, s0, ns), ChunkMulti{nullptr, 0, nullptr}, chunk_exact(ps),
+    return launch_bp_chunk(chunk_args(ps, pred, stats, s0, ns), ChunkMulti{nullptr, 0, nullptr}, bp_exact(ps),
                            ps.cs.wide, bp_grid, ps.P, ps.bp_lds, stream);
+  if (ps.stream)
+    return launch_bp_stream(stream_args(ps, pred, stats, s0, ns), StreamMulti{nullptr, 0, nullptr}, ps.ss.cap, bp_grid, ps.P, ps.bp_lds,
+                            stream);
   const BPArgs a = bp_args(ps, pred, stats, s0, ns);
   const BPMulti none{nullptr, 0, nullptr};
   if (ps.lanes)
@@ -1567,6 +1635,10 @@ struct MultiDecode {
     bool inlds = false, wide = false, exact = false;
     ChunkArgs* ctab = nullptr;       // inlds: device [items]
     ChunkArgs cfirst{};
+    bool stream = false;
+    int cap = 0;                     // stream: ring capacity
+    StreamArgs* stab = nullptr;      // stream: device [items]
+    StreamArgs sfirst{};
     unsigned char* slab = nullptr;   // lanes: the state of every workgroup, shared by the group's items
     int P = 0, grid = 0;
     size_t lds = 0;
@@ -1597,7 +1669,7 @@ struct MultiDecode {
 
 void decode_multi_free(MultiDecode* m) {
   if (!m) return;
-  for (auto& g : m->bp) { hipFree(g.tab); hipFree(g.ctab); hipFree(g.slab); }
+  for (auto& g : m->bp) { hipFree(g.tab); hipFree(g.ctab); hipFree(g.stab); hipFree(g.slab); }
   hipFree(m->osd_tab);
   hipFree(m->osd_tab2);
   hipFree(m->next);
@@ -1629,7 +1701,7 @@ tmcs_status decode_multi_create(const std::vector<MultiItemSpec>& specs, uint64_
     MultiDecode::BPGroup* g = nullptr;
     for (auto& q : m->bp)
       if (q.gstate == ps.gstate && q.lanes == ps.lanes && q.fused == ps.fused && q.pk == ps.pk && q.P == ps.P &&
-          q.inlds == ps.inlds && (!ps.inlds || q.wide == ps.cs.wide)) g = &q;
+          q.inlds == ps.inlds && q.stream == ps.stream && q.cap == ps.ss.cap && (!ps.inlds || q.wide == ps.cs.wide)) g = &q;
     if (!g) {
       m->bp.push_back(MultiDecode::BPGroup());
       g = &m->bp.back();
@@ -1638,15 +1710,17 @@ tmcs_status decode_multi_create(const std::vector<MultiItemSpec>& specs, uint64_
       g->fused = ps.fused;
       g->pk = ps.pk;
       g->inlds = ps.inlds;
+      g->stream = ps.stream;
+      g->cap = ps.ss.cap;
       g->wide = ps.inlds && ps.cs.wide;
       g->P = ps.P;
       g->grid = ps.bp_grid_max;
     }
     g->items.push_back(i);
     g->weighted = g->weighted || ps.cfg.weights_dev != nullptr;
-    g->exact = g->exact || chunk_exact(ps);
+    g->exact = g->exact || bp_exact(ps);
     g->grid = std::min(g->grid, ps.bp_grid_max);
-    if (ps.inlds) g->lds = std::max(g->lds, ps.bp_lds);
+    if (ps.inlds || ps.stream) g->lds = std::max(g->lds, ps.bp_lds);
   }
   // Heaviest items first in every group (workgroups take the items in order):
   // the launch then ends on the cheapest shots instead of waiting for the last
@@ -1664,7 +1738,7 @@ tmcs_status decode_multi_create(const std::vector<MultiItemSpec>& specs, uint64_
   const int cus = device_cus();
   for (auto& g : m->bp) {
     if (g.inlds) {
-      g.grid = std::min(g.grid, cus * chunk_teams(g.lds, g.P));
+      g.grid = std::min(g.grid, cus * lds_teams(g.lds + CHUNK_LDS_STATIC, g.P));
       std::vector<ChunkArgs> tab;
       for (int i : g.items) {
         const auto& it = m->items[i];
@@ -1672,6 +1746,18 @@ tmcs_status decode_multi_create(const std::vector<MultiItemSpec>& specs, uint64_
       }
       g.cfirst = tab[0];
       if ((st = upload(&g.ctab, tab)) != TMCS_OK) { decode_multi_free(m); return st; }
+      continue;
+    }
+    if (g.stream) {
+      // (never more than any item's slabs hold: every item's grid is at least this)
+      g.grid = std::min(g.grid, cus * lds_teams(g.lds, g.P));
+      std::vector<StreamArgs> tab;
+      for (int i : g.items) {
+        const auto& it = m->items[i];
+        tab.push_back(stream_args(it.ps, it.pred, it.stats, 0, (int64_t)batch));
+      }
+      g.sfirst = tab[0];
+      if ((st = upload(&g.stab, tab)) != TMCS_OK) { decode_multi_free(m); return st; }
       continue;
     }
     if (g.lanes) {
@@ -1771,6 +1857,11 @@ tmcs_status decode_multi_enqueue(MultiDecode* m, hipStream_t stream) {
     if (g.inlds) {
       const ChunkMulti cmu{g.ctab, (int32_t)g.items.size(), m->next};
       if ((st = launch_bp_chunk(g.cfirst, cmu, g.exact, g.wide, grid, g.P, g.lds, stream)) != TMCS_OK) return st;
+      continue;
+    }
+    if (g.stream) {
+      const StreamMulti smu{g.stab, (int32_t)g.items.size(), m->next};
+      if ((st = launch_bp_stream(g.sfirst, smu, g.cap, grid, g.P, g.lds, stream)) != TMCS_OK) return st;
       continue;
     }
     const BPArgs& a0 = g.first;
