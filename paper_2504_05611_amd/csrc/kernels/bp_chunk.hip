@@ -132,8 +132,10 @@ __global__ void __launch_bounds__(1024, 8) k_bp_chunk(ChunkArgs, ChunkMulti mu) 
   if (tid < 4) s_cnt[tid] = 0ull;
   auto flush = [&]() {
     __syncthreads();
-    tmcs_decode_stats* const stats = reread(a)->stats;
+    // (as many copies of the statistics as spare the teams waiting on each other's adds)
+    tmcs_decode_stats* stats = reread(a)->stats;
     if (stats) {
+      stats += blockIdx.x % STAT_SHARDS;
       for (int i = tid; i < TMCS_BP_HIST_BINS; i += P)
         if (s_hist[i]) atomicAdd((unsigned long long*)&stats->bp_iter_hist[i], (unsigned long long)s_hist[i]);
       if (tid == 0) {
@@ -152,10 +154,10 @@ __global__ void __launch_bounds__(1024, 8) k_bp_chunk(ChunkArgs, ChunkMulti mu) 
   // counter, several at a time: a counter gives out about 85 values a
   // microsecond, fewer than the teams of a small DEM finish shots (d = 5: 5.7
   // instead of 10.7 ms per 10^6 shots), and as many teams as there are shots
-  // never ask for one.  A batch leaves every team some sixteen turns, so the
-  // launch still ends evenly.
+  // never ask for one.  Batches grow with the number of teams (small DEMs, short
+  // shots); with few teams they stay at one shot, so that the launch ends evenly.
   int ticket = (int)blockIdx.x, left = 0;
-  const int batch = max(1, min(16, (total - (int)gridDim.x) / (16 * (int)gridDim.x)));
+  const int batch = max(1, (int)gridDim.x / 1024);
   auto take = [&]() {
     if (left == 0) {
       ticket = total > (int)gridDim.x ? (int)gridDim.x + atomicAdd(MULTI ? mu.next : &a->counters[1], batch) : total;

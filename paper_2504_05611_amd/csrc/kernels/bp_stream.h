@@ -66,7 +66,7 @@ struct StreamArgs {
   int32_t* osd_queue;
   float* osd_llr;            // [chunk][n]
   uint64_t* pred;            // [k][stride]
-  tmcs_decode_stats* stats;
+  tmcs_decode_stats* stats;  // [STAT_SHARDS]
   uint8_t* ehat;
   float* llr;
   int32_t* iters;

@@ -144,8 +144,10 @@ __global__ void __launch_bounds__(1024, 8) k_bp_stream(StreamArgs, StreamMulti m
   if (tid < 4) sh.cnt[tid] = 0ull;
   auto flush = [&]() {
     __syncthreads();
-    tmcs_decode_stats* const stats = reread(a)->stats;
+    // (as many copies of the statistics as spare the teams waiting on each other's adds)
+    tmcs_decode_stats* stats = reread(a)->stats;
     if (stats) {
+      stats += blockIdx.x % STAT_SHARDS;
       for (int i = tid; i < TMCS_BP_HIST_BINS; i += P)
         if (sh.hist[i]) atomicAdd((unsigned long long*)&stats->bp_iter_hist[i], (unsigned long long)sh.hist[i]);
       if (tid == 0) {

@@ -79,7 +79,7 @@ struct DecodeDevice {
   std::vector<Sched> scheds;
   std::vector<ChunkSched> chunks;   // schedules of the LDS-state kernel, one per team size used so far
   double log_start = 30.0;          // log10 of the largest magnitude BP starts from
-  int chunk_P = 0;                  // its default team size (-1: the state does not fit)
+  int64_t chunk_lds = 0;            // LDS bytes of a team, about (-1: the state does not fit)
   std::vector<StreamSched> streams; // schedules of the streaming kernel, one per team size used so far
   std::vector<int> no_stream;       // team sizes it does not take this DEM with
   float* cw = nullptr;              // per-edge weights by schedule step
@@ -91,6 +91,7 @@ struct DecodeDevice {
   float* osd_llr = nullptr;
   uint64_t* basis = nullptr;
   uint64_t* synd = nullptr;
+  uint64_t* shards = nullptr;      // [STAT_SHARDS] statistics of the pass
   unsigned char* gstate = nullptr;  // BP state in device memory, one slab per team
   int32_t* rowmap = nullptr;        // windowed OSD: [grid][2][m] row tables (WIN_NONE between shots)
   int32_t* retry = nullptr;         // OSD jobs the sorted prefix did not settle
@@ -103,17 +104,30 @@ __global__ void k_zero_words(uint64_t* p, int64_t n) {
     p[i] = 0ull;
 }
 
-__global__ void k_add_shots(tmcs_decode_stats* stats, unsigned long long n) {
-  if (threadIdx.x == 0) atomicAdd((unsigned long long*)&stats->shots, n);
+// Start of a decoder pass: the predictions (first pass of a call), the pass's
+// counters and the copies of its statistics.
+constexpr int STAT_WORDS = (int)(sizeof(tmcs_decode_stats) / sizeof(uint64_t));
+__global__ void k_begin_pass(uint64_t* pred, int64_t n, int32_t* counters, uint64_t* shards) {
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t i = i0; i < n; i += (int64_t)gridDim.x * blockDim.x) pred[i] = 0ull;
+  if (i0 < 8) counters[i0] = 0;
+  for (int64_t i = i0; i < STAT_SHARDS * STAT_WORDS; i += (int64_t)gridDim.x * blockDim.x) shards[i] = 0ull;
 }
 
-// Shots the compaction left out (all-zero syndrome) are converged: their
-// all-zero hard decision satisfies s, as on the path that visits every shot.
-__global__ void k_add_trivial(tmcs_decode_stats* stats, const int32_t* counters, unsigned long long n) {
-  if (threadIdx.x != 0) return;
-  const unsigned long long t = n - (unsigned long long)counters[0];
-  atomicAdd((unsigned long long*)&stats->converged, t);
-  atomicAdd((unsigned long long*)&stats->bp_iter_hist[0], t);
+// After BP: the pass's statistics onto the caller's.  Shots the compaction left
+// out (all-zero syndrome) are converged: their all-zero hard decision satisfies
+// s, as on the path that visits every shot.
+__global__ void __launch_bounds__(128) k_finish_stats(tmcs_decode_stats* stats, const uint64_t* shards, const int32_t* counters,
+                                                      unsigned long long shots, int compacted) {
+  static_assert(STAT_WORDS <= 128, "one thread per word");
+  const int i = threadIdx.x;
+  if (i >= STAT_WORDS) return;
+  unsigned long long x = 0ull;
+  for (int k = 0; k < STAT_SHARDS; ++k) x += shards[k * STAT_WORDS + i];
+  const unsigned long long trivial = compacted ? shots - (unsigned long long)counters[0] : 0ull;
+  if (i == (int)(offsetof(tmcs_decode_stats, shots) / 8)) x += shots;
+  if (i == (int)(offsetof(tmcs_decode_stats, converged) / 8) || i == (int)(offsetof(tmcs_decode_stats, bp_iter_hist) / 8)) x += trivial;
+  if (x) atomicAdd((unsigned long long*)stats + i, x);
 }
 
 __global__ void k_zero_i32(int32_t* p, int n) {
@@ -157,57 +171,44 @@ __global__ void __launch_bounds__(64) k_synd_transpose(const uint64_t* __restric
   }
 }
 
-// Queue the shots of the chunk whose syndrome is non-zero.  Same-address
-// atomics serialise, so a workgroup (256 lanes) takes tiles of 16 x 256 shots
-// and reserves the queue slots of a whole tile with one atomic.
-constexpr int COMPACT_SLABS = 16;
-__global__ void __launch_bounds__(256) k_compact(const uint64_t* __restrict__ synd, int32_t mw, int64_t nshots,
+// Queue the shots of the chunk whose syndrome is non-zero.  Same-address atomics
+// serialise (about 85 a microsecond), so a workgroup marks a tile of shots in LDS,
+// reading their words in order, and reserves the tile's queue slots with one
+// atomic; the host picks the tile.
+constexpr int COMPACT_MAX = 4096;
+__global__ void __launch_bounds__(256) k_compact(const uint64_t* __restrict__ synd, int32_t mw, int64_t nshots, int32_t tile,
                                                  int32_t* __restrict__ queue, int32_t* __restrict__ counters) {
+  __shared__ uint8_t s_any[COMPACT_MAX];
   __shared__ int s_wave[4];
   __shared__ int s_base;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const uint64_t below = (1ull << lane) - 1ull;
-  constexpr int64_t TILE = 256 * COMPACT_SLABS;
-  for (int64_t t0 = (int64_t)blockIdx.x * TILE; t0 < nshots; t0 += (int64_t)gridDim.x * TILE) {
-    uint64_t keep[COMPACT_SLABS];
-    int tot = 0;
-#pragma unroll
-    for (int i = 0; i < COMPACT_SLABS; ++i) {
-      const int64_t sh = t0 + i * 256 + threadIdx.x;
-      uint64_t any = 0ull;
-      if (sh < nshots)
-        for (int k = 0; k < mw; ++k) any |= synd[sh * mw + k];
-      keep[i] = __ballot(any != 0ull);
-      tot += __popcll(keep[i]);
-    }
-    if (lane == 0) s_wave[wv] = tot;
-    __syncthreads();
-    if (threadIdx.x == 0) s_base = atomicAdd(&counters[0], s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3]);
-    __syncthreads();
-    int base = s_base;
-    for (int w = 0; w < wv; ++w) base += s_wave[w];
-#pragma unroll
-    for (int i = 0; i < COMPACT_SLABS; ++i) {
-      if ((keep[i] >> lane) & 1ull) queue[base + __popcll(keep[i] & below)] = (int32_t)(t0 + i * 256 + threadIdx.x);
-      base += __popcll(keep[i]);
-    }
-    __syncthreads();   // s_wave and s_base are rewritten for the next tile
-  }
-}
-
-// The same for wide syndromes (many detector words per shot, few shots per
-// call, as in the large surface-code CNOTs): one wave per shot, its lanes
-// reading the shot's words together, one queue slot per kept shot.  The queue
-// order differs from k_compact's; every shot is decoded on its own, so nothing
-// depends on it.
-__global__ void __launch_bounds__(256) k_compact_wide(const uint64_t* __restrict__ synd, int32_t mw, int64_t nshots,
-                                                      int32_t* __restrict__ queue, int32_t* __restrict__ counters) {
-  const int lane = threadIdx.x & 63;
-  const int64_t waves = (int64_t)gridDim.x * 4;
-  for (int64_t sh = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); sh < nshots; sh += waves) {
-    uint64_t any = 0ull;
-    for (int k = lane; k < mw; k += 64) any |= synd[sh * mw + k];
-    if (__ballot(any != 0ull) && lane == 0) queue[atomicAdd(&counters[0], 1)] = (int32_t)sh;
+  const int64_t t0 = (int64_t)blockIdx.x * tile;
+  const int nt = (int)min((int64_t)tile, nshots - t0);
+  for (int i = tid; i < tile; i += 256) s_any[i] = 0;
+  __syncthreads();
+  const uint64_t* p = synd + t0 * mw;
+  const uint32_t words = (uint32_t)nt * (uint32_t)mw;
+#pragma unroll 4
+  for (uint32_t i = tid; i < words; i += 256)
+    if (p[i]) s_any[i / (uint32_t)mw] = 1;       // (every writer stores 1)
+  __syncthreads();
+  // waves take consecutive runs of 64 shots
+  const int runs = (tile + 63) / 64, per = (runs + 3) / 4, r0 = wv * per, r1 = min(runs, r0 + per);
+  int tot = 0;
+  for (int r = r0; r < r1; ++r) tot += __popcll(__ballot(r * 64 + lane < nt && s_any[min(r * 64 + lane, COMPACT_MAX - 1)]));
+  if (lane == 0) s_wave[wv] = tot;
+  __syncthreads();
+  if (tid == 0) s_base = atomicAdd(&counters[0], s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3]);
+  __syncthreads();
+  int base = s_base;
+  for (int w = 0; w < wv; ++w) base += s_wave[w];
+  for (int r = r0; r < r1; ++r) {
+    const int i = r * 64 + lane;
+    const bool keep = i < nt && s_any[min(i, COMPACT_MAX - 1)];
+    const uint64_t b = __ballot(keep);
+    if (keep) queue[base + __popcll(b & below)] = (int32_t)(t0 + i);
+    base += __popcll(b);
   }
 }
 
@@ -652,7 +653,7 @@ tmcs_status grow(T** p, size_t* cap, size_t need) {
 
 void free_device(DecodeDevice* d) {
   hipFree(d->row_ptr); hipFree(d->col_idx); hipFree(d->col_ptr); hipFree(d->csc_row); hipFree(d->csc_edge);
-  hipFree(d->lam); hipFree(d->obs_mask); hipFree(d->counters); hipFree(d->queue); hipFree(d->osd_queue);
+  hipFree(d->lam); hipFree(d->obs_mask); hipFree(d->counters); hipFree(d->shards); hipFree(d->queue); hipFree(d->osd_queue);
   hipFree(d->osd_llr); hipFree(d->basis); hipFree(d->synd); hipFree(d->gstate); hipFree(d->init); hipFree(d->sign0);
   hipFree(d->rowmap); hipFree(d->retry); hipFree(d->lone);
   for (auto& q : d->scheds) {
@@ -750,7 +751,8 @@ tmcs_status build_state(const Dem& D, int dev, DecodeDevice** out) {
     delete d;
     return st;
   }
-  if (hipMalloc((void**)&d->counters, 8 * sizeof(int32_t)) != hipSuccess) {
+  if (hipMalloc((void**)&d->counters, 8 * sizeof(int32_t)) != hipSuccess ||
+      hipMalloc((void**)&d->shards, STAT_SHARDS * sizeof(tmcs_decode_stats)) != hipSuccess) {
     free_device(d);
     delete d;
     return fail(TMCS_ENOMEM, "hipMalloc failed (counters)");
@@ -1090,6 +1092,25 @@ tmcs_status get_stream(const Dem& D, DecodeDevice* d, int P, bool* ok, StreamSch
 // Teams of P lanes that one compute unit holds with lds bytes of LDS each.
 int lds_teams(size_t lds, int P) { return std::max(1, std::min((int)((160 * 1024) / lds), 32 / (P / 64))); }
 
+// Lanes of a team of the LDS-state kernel, where a CU's LDS holds `fit` teams.
+// With shots enough for all of them, about 28 waves per CU in as many teams as
+// fit (more waves overlap more of the waits on LDS and records; fewer teams per
+// CU would leave lanes of narrow graphs idle).  With s shots per CU a team
+// should still see several, or its start and end and the last shot's iterations
+// set the time: about sqrt(s) teams, whose waves share a shot.  Measured (waves
+// per team: us): d = 5, 10^6 shots 1: 6300, 2: 5550, 3: 5900, 4: 5900; 32,768
+// shots 1: 676, 2: 506, 4: 377, 8: 470; 4432 shots 2: 240, 4: 200, 8: 186, 12:
+// 177; 64 shots 2: 144, 4: 86, 16: 73.  BB [[144,12,12]] memory of 3 rounds, 4432
+// shots 3: 593, 4: 476, 8: 325, 16: 441; of 12 rounds (fit 2), 32,768 shots 8:
+// 9840, 12: 8540, 16: 8420.  Waves beyond the column chunks would only wait.
+int chunk_team(const Dem& D, int fit, uint64_t n_shots, int cus, int* teams) {
+  *teams = 1;
+  for (uint64_t s = n_shots / (uint64_t)cus; s >= 4; s >>= 2) *teams *= 2;
+  *teams = std::min(*teams, fit);
+  const int waves = *teams == fit ? (fit <= 2 ? 16 : 28 / fit) : 32 / *teams;
+  return 64 * std::max(1, std::min({16, waves, std::max(2, (D.cols + 63) / 64)}));
+}
+
 // The device state cached on the DEM handle (rebuilt when the device changes).
 tmcs_status ensure_device(const Dem& dc, DecodeDevice** out) {
   Dem& D = const_cast<Dem&>(dc);
@@ -1215,24 +1236,15 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
     return fail(TMCS_EUNSUPPORTED, "OSD-CS needs the dense elimination (<= 2048 detectors, <= 16384 columns)");
   const int cus = device_cus();
   // state in LDS wherever it fits
-  int chunk_P = -1;
+  int chunk_P = -1, teams = 32;
   if (cfg.bp_global_state == 0) {
-    if (d->chunk_P == 0) {
-      // up to 28 waves per CU: the passes wait on LDS and on their records, and
-      // more waves overlap more; one or two teams take all 16 each.  Measured
-      // (waves: ms): d = 5, 15 teams per CU, 1: 6.30, 2: 5.58, 3: 5.87 per 10^6
-      // shots; BB [[144,12,12]] memory, 2 teams, 8: 19.4, 12: 17.2, 16: 17.1 per
-      // 65,536; d = 11, 1 team, 12: 0.44, 16: 0.40 per 1021
+    if (d->chunk_lds == 0) {
       size_t lds = 0;
-      d->chunk_P = -1;
-      if (chunk_fits(D, 512, &lds)) {
-        const int teams = lds_teams(lds + CHUNK_LDS_STATIC, 64);
-        d->chunk_P = 64 * (teams <= 2 ? 16 : std::max(1, std::min(16, 28 / teams)));
-      }
+      d->chunk_lds = chunk_fits(D, 512, &lds) ? (int64_t)(lds + CHUNK_LDS_STATIC) : -1;
     }
-    chunk_P = d->chunk_P;
-    if (chunk_P > 0 && cfg.bp_threads > 0) chunk_P = std::min(1024, std::max(64, (cfg.bp_threads + 63) / 64 * 64));
-    if (chunk_P > 0) {
+    if (d->chunk_lds > 0) {
+      chunk_P = cfg.bp_threads > 0 ? std::min(1024, std::max(64, (cfg.bp_threads + 63) / 64 * 64))
+                                   : chunk_team(D, lds_teams((size_t)d->chunk_lds, 64), n_shots, cus, &teams);
       if ((st = get_chunk(D, d, chunk_P, &ps.cs)) != TMCS_OK) return st;
       if (ps.cs.lds() + CHUNK_LDS_STATIC > 160 * 1024) chunk_P = -1;
     }
@@ -1296,8 +1308,7 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
   if (ps.inlds) {
     ps.P = chunk_P;
     ps.bp_lds = ps.cs.lds();
-    const int fit = lds_teams(ps.bp_lds + CHUNK_LDS_STATIC, chunk_P);
-    ps.bp_grid_max = cus * (cfg.bp_per_cu > 0 ? std::min(fit, cfg.bp_per_cu) : fit);
+    ps.bp_grid_max = cus * std::min(cfg.bp_per_cu > 0 ? cfg.bp_per_cu : teams, lds_teams(ps.bp_lds + CHUNK_LDS_STATIC, chunk_P));
     if (cfg.weights_dev &&
         (st = grow(&d->cw, &d->cap_cw, ((size_t)std::max(cfg.max_iter, 1) * (ps.cs.vrows + ps.cs.crows) + CHUNK_PAD_ROWS) * 64)) != TMCS_OK)
       return st;
@@ -1506,44 +1517,40 @@ OSDArgs osd_args(const DecodePass& ps, uint64_t* pred, tmcs_decode_stats* stats,
   return o;
 }
 
-// Zero the predictions of a pass (all chunks).
-void decode_zero_pred(const DecodePass& ps, uint64_t* pred, hipStream_t stream) {
-  const int64_t total_words = (int64_t)ps.D->nobs * ps.stride;
-  if (total_words) {
-    const int64_t g = std::min<int64_t>((total_words + 255) / 256, 4096);
-    TMCS_LAUNCH("k_zero_words", k_zero_words, dim3((unsigned)g), dim3(256), 0, stream, pred, total_words);
+// Syndrome staging of the chunk [s0, s0 + ns): predictions (first chunk),
+// counters and statistics cleared, shot-major transpose, compaction of the
+// non-trivial shots.
+void decode_stage(const DecodePass& ps, const uint64_t* det, uint64_t* pred, int64_t s0, int64_t ns, hipStream_t stream) {
+  DecodeDevice* d = ps.d;
+  const Dem& D = *ps.D;
+  {
+    const int64_t words = s0 == 0 ? (int64_t)D.nobs * ps.stride : 0;
+    const int64_t g = std::max<int64_t>(1, std::min<int64_t>((words + 255) / 256, 4096));
+    TMCS_LAUNCH("k_begin_pass", k_begin_pass, dim3((unsigned)g), dim3(256), 0, stream, pred, words, d->counters, d->shards);
+  }
+  const int mw = std::max(ps.mw, 1);
+  {
+    const int64_t nw = (ns + 63) / 64;
+    const int64_t gx = (nw + N_XCD - 1) / N_XCD * N_XCD;
+    TMCS_LAUNCH("k_synd_transpose", k_synd_transpose, dim3((unsigned)gx, (unsigned)((mw + SYND_TILES - 1) / SYND_TILES)),
+                dim3(64), 0, stream, det, D.rows, ps.stride, s0, ns, mw, d->synd);
+  }
+  if (!ps.full) {
+    // the smallest tile that leaves at most 512 of them (each costs an atomic on
+    // the queue's length; a larger one leaves CUs idle)
+    int tile = 64;
+    while (tile < COMPACT_MAX && ns > (int64_t)tile * 512) tile *= 2;
+    TMCS_LAUNCH("k_compact", k_compact, dim3((unsigned)((ns + tile - 1) / tile)), dim3(256), 0, stream, d->synd, mw, ns, tile,
+                d->queue, d->counters);
   }
 }
 
-// Syndrome staging of the chunk [s0, s0 + ns): counters reset, shot-major
-// transpose, compaction of the non-trivial shots.
-void decode_stage(const DecodePass& ps, const uint64_t* det, tmcs_decode_stats* stats, int64_t s0, int64_t ns,
-                  hipStream_t stream) {
-  DecodeDevice* d = ps.d;
-  const Dem& D = *ps.D;
-  TMCS_LAUNCH("k_zero_i32", k_zero_i32, dim3(1), dim3(64), 0, stream, d->counters, 8);
-  if (stats) TMCS_LAUNCH("k_add_shots", k_add_shots, dim3(1), dim3(1), 0, stream, stats, (unsigned long long)ns);
-  const int mw = ps.mw;
-  {
-    const int64_t nw = (ns + 63) / 64;
-    const int mt = std::max(mw, 1);
-    const int64_t gx = (nw + N_XCD - 1) / N_XCD * N_XCD;
-    TMCS_LAUNCH("k_synd_transpose", k_synd_transpose, dim3((unsigned)gx, (unsigned)((mt + SYND_TILES - 1) / SYND_TILES)),
-                dim3(64), 0, stream, det, D.rows, ps.stride, s0, ns, mt, d->synd);
-  }
-  if (!ps.full) {
-    if (mw >= 64) {
-      const int64_t g = std::min<int64_t>((ns + 3) / 4, 4096);
-      TMCS_LAUNCH("k_compact", k_compact_wide, dim3((unsigned)g), dim3(256), 0, stream, d->synd, mw, ns, d->queue,
-                  d->counters);
-    } else {
-      const int64_t g = std::min<int64_t>((ns + 256 * COMPACT_SLABS - 1) / (256 * COMPACT_SLABS), 1024);
-      TMCS_LAUNCH("k_compact", k_compact, dim3((unsigned)g), dim3(256), 0, stream, d->synd, std::max(mw, 1), ns,
-                  d->queue, d->counters);
-    }
-    if (stats) TMCS_LAUNCH("k_add_trivial", k_add_trivial, dim3(1), dim3(1), 0, stream, stats, d->counters,
-                           (unsigned long long)ns);
-  }
+// After the pass's BP launch: its statistics onto the caller's.
+tmcs_status decode_finish_stats(const DecodePass& ps, tmcs_decode_stats* stats, int64_t ns, hipStream_t stream) {
+  if (!stats) return TMCS_OK;
+  TMCS_LAUNCH("k_finish_stats", k_finish_stats, dim3(1), dim3(128), 0, stream, stats, (const uint64_t*)ps.d->shards, ps.d->counters,
+              (unsigned long long)ns, ps.full ? 0 : 1);
+  return hip_check(hipGetLastError(), "k_finish_stats launch");
 }
 
 tmcs_status decode_bp_launch(const DecodePass& ps, uint64_t* pred, tmcs_decode_stats* stats, int64_t s0, int64_t ns,
@@ -1606,12 +1613,12 @@ tmcs_status decode_run(const Dem& D, const tmcs_decoder_cfg& cfg, const uint64_t
   DecodePass ps;
   tmcs_status st = decode_prepare(D, cfg, n_shots, state, stream, &ps);
   if (st != TMCS_OK) return st;
-  decode_zero_pred(ps, pred, stream);
   if ((st = chunk_weights(ps, stream)) != TMCS_OK) return st;
   for (int64_t s0 = 0; s0 < (int64_t)n_shots; s0 += ps.chunk) {
     const int64_t ns = std::min<int64_t>(ps.chunk, (int64_t)n_shots - s0);
-    decode_stage(ps, det, stats, s0, ns, stream);
-    if ((st = decode_bp_launch(ps, pred, stats, s0, ns, stream)) != TMCS_OK) return st;
+    decode_stage(ps, det, pred, s0, ns, stream);
+    if ((st = decode_bp_launch(ps, pred, stats ? (tmcs_decode_stats*)ps.d->shards : nullptr, s0, ns, stream)) != TMCS_OK) return st;
+    if ((st = decode_finish_stats(ps, stats, ns, stream)) != TMCS_OK) return st;
     if ((st = decode_osd_launch(ps, pred, stats, s0, stream)) != TMCS_OK) return st;
   }
   return TMCS_OK;
@@ -1629,6 +1636,7 @@ struct MultiDecode {
     const uint64_t* det = nullptr;
     uint64_t* pred = nullptr;
     tmcs_decode_stats* stats = nullptr;
+    tmcs_decode_stats* bp_stats() const { return stats ? (tmcs_decode_stats*)ps.d->shards : nullptr; }
   };
   struct BPGroup {
     bool gstate = false, lanes = false, fused = false, pk = false, weighted = false;
@@ -1695,6 +1703,29 @@ tmcs_status decode_multi_create(const std::vector<MultiItemSpec>& specs, uint64_
     if (st != TMCS_OK) { decode_multi_free(m); return st; }
     m->items.push_back(it);
   }
+  // Items with their state in LDS share one team size, that of the heaviest, and
+  // so one launch (unless the caller asked for another).
+  {
+    int common = 0;
+    int64_t most = -1;
+    for (const auto& it : m->items)
+      if (it.ps.inlds && it.ps.cfg.bp_threads <= 0 && it.ps.D->edges > most) {
+        most = it.ps.D->edges;
+        common = it.ps.P;
+      }
+    for (size_t i = 0; i < m->items.size(); ++i) {
+      auto& it = m->items[i];
+      if (!it.ps.inlds || it.ps.cfg.bp_threads > 0 || it.ps.P == common) continue;
+      tmcs_decoder_cfg cfg = specs[i].cfg;
+      cfg.bp_threads = common;
+      DecodePass again;
+      if ((st = decode_prepare(*specs[i].D, cfg, batch, specs[i].state, stream, &again, true)) != TMCS_OK) {
+        decode_multi_free(m);
+        return st;
+      }
+      if (again.inlds) it.ps = again;
+    }
+  }
   // BP groups: (state placement, team size)
   for (int i = 0; i < (int)m->items.size(); ++i) {
     const DecodePass& ps = m->items[i].ps;
@@ -1742,7 +1773,7 @@ tmcs_status decode_multi_create(const std::vector<MultiItemSpec>& specs, uint64_
       std::vector<ChunkArgs> tab;
       for (int i : g.items) {
         const auto& it = m->items[i];
-        tab.push_back(chunk_args(it.ps, it.pred, it.stats, 0, (int64_t)batch));
+        tab.push_back(chunk_args(it.ps, it.pred, it.bp_stats(), 0, (int64_t)batch));
       }
       g.cfirst = tab[0];
       if ((st = upload(&g.ctab, tab)) != TMCS_OK) { decode_multi_free(m); return st; }
@@ -1754,7 +1785,7 @@ tmcs_status decode_multi_create(const std::vector<MultiItemSpec>& specs, uint64_
       std::vector<StreamArgs> tab;
       for (int i : g.items) {
         const auto& it = m->items[i];
-        tab.push_back(stream_args(it.ps, it.pred, it.stats, 0, (int64_t)batch));
+        tab.push_back(stream_args(it.ps, it.pred, it.bp_stats(), 0, (int64_t)batch));
       }
       g.sfirst = tab[0];
       if ((st = upload(&g.stab, tab)) != TMCS_OK) { decode_multi_free(m); return st; }
@@ -1774,7 +1805,7 @@ tmcs_status decode_multi_create(const std::vector<MultiItemSpec>& specs, uint64_
     std::vector<BPArgs> tab;
     for (int i : g.items) {
       const auto& it = m->items[i];
-      tab.push_back(bp_args(it.ps, it.pred, it.stats, 0, (int64_t)batch));
+      tab.push_back(bp_args(it.ps, it.pred, it.bp_stats(), 0, (int64_t)batch));
       if (g.lanes) {
         tab.back().gstate = g.slab;
         tab.back().team_bytes = g.lds;
@@ -1842,8 +1873,7 @@ tmcs_status decode_multi_create(const std::vector<MultiItemSpec>& specs, uint64_
 tmcs_status decode_multi_enqueue(MultiDecode* m, hipStream_t stream) {
   const int64_t ns = (int64_t)m->batch;
   for (auto& it : m->items) {
-    decode_zero_pred(it.ps, it.pred, stream);
-    decode_stage(it.ps, it.det, it.stats, 0, ns, stream);
+    decode_stage(it.ps, it.det, it.pred, 0, ns, stream);
   }
   TMCS_LAUNCH("k_zero_i32", k_zero_i32, dim3(1), dim3(64), 0, stream, m->next, 3);
   tmcs_status st;
@@ -1876,6 +1906,8 @@ tmcs_status decode_multi_enqueue(MultiDecode* m, hipStream_t stream) {
     launch_k_bp<true>(g.weighted, g.pk, grid, g.P, stream, a0, mu);
     if ((st = hip_check(hipGetLastError(), "k_bp launch")) != TMCS_OK) return st;
   }
+  for (auto& it : m->items)
+    if ((st = decode_finish_stats(it.ps, it.stats, ns, stream)) != TMCS_OK) return st;
   // Items outside the windowed launch (another window shape, or no window) take
   // their OSD on the side stream when there is one: the two chains then share
   // the GPU, and each one's full-window retries (a few shots, one workgroup each,

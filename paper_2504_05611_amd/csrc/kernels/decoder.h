@@ -98,6 +98,9 @@ __device__ __forceinline__ uint64_t block_xor_u64(uint64_t v, uint64_t* scratch)
   return r;
 }
 
+// Copies of a pass's statistics that BP adds to (k_finish_stats adds them up).
+constexpr int STAT_SHARDS = 16;
+
 // ------------------------------------------------------------------ BP
 // Schedule records of the BP passes (int4 = {x, y, z, w}).
 //   check pass: x = v | flags, y = CSR edge e, z = check c (edges of a check are

@@ -6,7 +6,10 @@
 
 #include <algorithm>
 #include <cstring>
+#include <map>
+#include <mutex>
 #include <type_traits>
+#include <utility>
 
 #include "../host/device.h"
 #include "../host/timing.h"
@@ -194,12 +197,26 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
   int32_t* fpos = WIN ? a.rowmap + (int64_t)blockIdx.x * 2 * a.m : nullptr;   // [m] first window position
   int32_t* lmap = WIN ? fpos + a.m : nullptr;                                  // [m] local row index
   int cur = -1;                                                                // MULTI: current item
+  // A workgroup's first job is its own number; the others come from the counter.
+  // (A counter gives out about 85 values a microsecond: thousands of workgroups
+  // asking for a first job took 50 us of every launch, most of them for none.)
+  int total = 0;                                                               // MULTI: thread 0's
   if constexpr (MULTI) {
     if (tid == 0) {
       s_pref[0] = 0;
       for (int i = 0; i < mu.n; ++i) s_pref[i + 1] = s_pref[i] + mu.tab[i].counters[mu.tab[i].cnt_total];
+      total = s_pref[mu.n];
     }
+  } else {
+    total = a.counters[a.cnt_total];
+    if ((int)blockIdx.x >= total) return;
   }
+  bool first_job = true;
+  auto next_job = [&]() -> int {                                               // thread 0
+    if (first_job) return (int)blockIdx.x;
+    if (total <= (int)gridDim.x) return total;
+    return (int)gridDim.x + atomicAdd(MULTI ? mu.next : &a.counters[a.cnt_next], 1);
+  };
   // acc = s + sum of the basis vectors pivoted on rows of s.  With a fully
   // reduced basis this is zero on every pivot row; its syndrome part is zero iff
   // s lies in the span of the kept columns, and its combination part then names
@@ -227,14 +244,15 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
   while (true) {
     if (tid == 0) {
       if constexpr (MULTI) {
-        const int g = atomicAdd(mu.next, 1);
+        const int g = next_job();
         int i = 0;
         while (i < mu.n && g >= s_pref[i + 1]) ++i;
         s_inst = i;
         s_job = i < mu.n ? g - s_pref[i] : 0;
       } else {
-        s_job = atomicAdd(&a.counters[a.cnt_next], 1);
+        s_job = next_job();
       }
+      first_job = false;
     }
     __syncthreads();
     const int jn = s_job;
@@ -251,7 +269,7 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
       }
     } else {
       __syncthreads();
-      if (jn >= a.counters[a.cnt_total]) break;
+      if (jn >= total) break;
     }
     const int job = a.jobs ? a.jobs[jn] : jn;
     const int64_t ls = a.osd_queue[job];
@@ -740,6 +758,24 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
   }
 }
 
+// The grid that is resident at once (at most `grid`): a workgroup keeps taking
+// jobs until there are none, so one that has to wait for a place only starts its
+// first job when the others are done.
+int resident_grid(const void* kernel, int threads, size_t lds, int grid) {
+  static std::mutex mu;
+  static std::map<std::pair<const void*, size_t>, int> known;
+  std::lock_guard<std::mutex> lock(mu);
+  auto it = known.find({kernel, lds});
+  if (it == known.end()) {
+    int dev = 0, cus = 0, per_cu = 0;
+    hipGetDevice(&dev);
+    hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds) != hipSuccess || per_cu < 1) per_cu = 1 << 10;
+    it = known.emplace(std::make_pair(kernel, lds), std::max(1, cus) * per_cu).first;
+  }
+  return std::max(1, std::min(grid, it->second));
+}
+
 template <int MW, int RW, int KPT, bool BL, bool PFX = false>
 tmcs_status launch_osd(const OSDArgs& a, int grid, size_t lds, hipStream_t s) {
   constexpr int NT = BL ? 64 : OSD_THREADS;
@@ -747,6 +783,7 @@ tmcs_status launch_osd(const OSDArgs& a, int grid, size_t lds, hipStream_t s) {
   if (lds > 64 * 1024 && hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
     return fail(TMCS_EUNSUPPORTED, "OSD workspace does not fit in LDS");
   // the full-sort pass over jobs a prefix left open is timed on its own
+  grid = resident_grid((const void*)k, NT, lds, grid);
   TMCS_LAUNCH(a.jobs ? "k_osd_retry" : "k_osd", k, dim3(grid), dim3(NT), lds, s, a, OSDMulti{nullptr, 0, nullptr});
   return hip_check(hipGetLastError(), "k_osd launch");
 }
@@ -818,6 +855,7 @@ tmcs_status launch_osd_win_t(const OSDArgs& a, const OSDMulti& mu, int grid, siz
   auto k = k_osd<MW, MW, WIN_KEYS / OSD_THREADS, false, OSD_THREADS, true, false, MULTI>;
   if (lds > 64 * 1024 && hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
     return fail(TMCS_EUNSUPPORTED, "OSD workspace does not fit in LDS");
+  grid = resident_grid((const void*)k, OSD_THREADS, lds, grid);
   TMCS_LAUNCH(a.jobs ? "k_osd_retry" : "k_osd", k, dim3(grid), dim3(OSD_THREADS), lds, s, a, mu);
   return hip_check(hipGetLastError(), "k_osd launch");
 }
