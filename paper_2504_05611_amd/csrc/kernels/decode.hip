@@ -1336,7 +1336,7 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
   const int osd_rows = osd_win ? WIN_MAX_ROWS : D.rows;
   if (osd_win) npad = WIN_KEYS;
   // (+ the OSD-CS bitset of kept sorted positions after the accumulator)
-  size_t osd_lds = (size_t)npad * 8 + (size_t)osd_rank * 8 + (size_t)osd_rows * 8 + (size_t)W * 8 + 64 +
+  size_t osd_lds = (size_t)npad * 8 + (size_t)osd_rank * 8 + (size_t)osd_rows * 4 + (size_t)W * 8 + 64 +
                    (cfg.osd_order > 0 ? (size_t)npad / 8 + 16 : 0);
   // small DEMs keep the elimination basis in LDS as well (at least two workgroups
   // per CU); their sorted keys are stored as 32-bit column indices
@@ -1355,7 +1355,7 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
   // (the one-wave variant gathers 8-byte keys over its 4-byte index area and the LDS basis after it)
   const bool osd_pfx = cfg.use_osd && !osd_win && cfg.osd_order == 0 && D.cols >= pfx_keys &&
                        (!osd_bl || (size_t)pfx_rank * W_pfx * 8 >= (size_t)pfx_keys * 4);
-  size_t pfx_lds = (size_t)pfx_keys * 8 + (size_t)pfx_rank * 8 + (size_t)osd_rows * 8 + (size_t)W_pfx * 8 + 64;
+  size_t pfx_lds = (size_t)pfx_keys * 8 + (size_t)pfx_rank * 8 + (size_t)osd_rows * 4 + (size_t)W_pfx * 8 + 64;
   if (osd_bl) pfx_lds += (size_t)pfx_rank * W_pfx * 8 - (size_t)pfx_keys * 4;
   const int osd_fit = std::max<int>(1, (int)((160 * 1024) / (osd_lds + 512)));
   const int osd_per_cu = std::min(osd_fit, cfg.osd_per_cu > 0 ? cfg.osd_per_cu : (osd_bl ? 16 : 4));
@@ -1383,7 +1383,7 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
   const int win1_rows = cfg.osd_window > 0 ? std::min(WIN_SMALL_ROWS, user_rows / 4) : 64 * mw1;
   const bool win2 = osd_win && win1_rows >= 2 && (cfg.osd_window > 0 || ev <= (mw1 == WIN_SMALL_MW ? 0.75 : 0.9) * win1_rows);
   const int W1 = 2 * mw1;
-  const size_t win1_lds = (size_t)WIN_KEYS * 8 + (size_t)(64 * mw1) * 16 + (size_t)W1 * 8 + 64;
+  const size_t win1_lds = (size_t)WIN_KEYS * 8 + (size_t)(64 * mw1) * 12 + (size_t)W1 * 8 + 64;
   const int win1_fit = std::max<int>(1, (int)((160 * 1024) / (win1_lds + 512)));
   const int win1_grid = std::max(1, cus * std::min(win1_fit, cfg.osd_per_cu > 0 ? cfg.osd_per_cu : 8));
   ps.osd_win = osd_win; ps.osd_pfx = osd_pfx; ps.osd_bl = osd_bl; ps.win2 = win2;

@@ -135,9 +135,22 @@ __device__ __forceinline__ uint64_t bit_of(const uint64_t (&v)[W], int p) {
 // The basis is kept fully reduced: basis vector i has a 1 at its pivot row p_i
 // and 0 at every other pivot row.  A candidate column h is then reduced by
 // XORing exactly the basis vectors whose pivot rows lie in supp(h) (at most the
-// column degree), and a syndrome s by those whose pivot rows lie in supp(s).
-// New basis vectors are created 64 at a time by one wave, made fully reduced
-// among themselves, and the older vectors are then reduced against them.
+// column degree).  New basis vectors are created up to 63 at a time by one wave,
+// made fully reduced among themselves, and the older vectors are then reduced
+// against them.
+//
+// The syndrome rides along in lane 63 of the wave that is creating them, so it is
+// reduced by each new vector like a candidate, at no cost, and OSD-0 stops at the
+// very column that completes the span.  Few columns are needed (median / largest
+// of 40 shots: BB [[144,12,12]] teleportation 27 / 169, memory at p = 2e-3 37 /
+// 112, weight-6 Pauli string 10 / 34); looking only after every 256 candidates
+// built 116 vectors a shot on the teleportation circuit, 2.2 us each with the
+// reductions that follow, where the chain of pivots is all there is to do.
+// Milliseconds before and after: 11.0 and 3.0 there (32768 shots, 36 % in OSD),
+// 1.7 and 0.33 on the Pauli string, 2.2 and 0.92 on the memory.
+// Combination words that no column has reached yet are zero and left out in the
+// variants that stop early (those that run to full rank lose more by the branch
+// per word: 51 instead of 36 ms of OSD-CS on 8192 shots of that circuit).
 // BL: the basis lives in LDS (after the sort keys) instead of HBM.
 // NT: threads per workgroup (64: one wave decodes a shot on its own).
 //
@@ -178,15 +191,17 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
   int32_t* pivot = (int32_t*)(BL ? lbasis + (size_t)a.rank * W : keys + a.npad);   // [rank] pivot row of basis i
   int32_t* kept = pivot + cap_r;                                   // [rank] column of basis i
   int32_t* prow = kept + cap_r;                                    // [m] basis index of a pivot row, or -1
-  int32_t* srow = prow + cap_m;                                    // [m] rows with a syndrome bit
   // (an offset from sm, not an integer cast, so that the compiler keeps LDS addressing)
-  const size_t acc_off = ((size_t)((unsigned char*)(srow + cap_m) - sm) + 7) & ~(size_t)7;
-  uint64_t* acc = (uint64_t*)(sm + acc_off);                       // [W] solve accumulator
+  const size_t acc_off = ((size_t)((unsigned char*)(prow + cap_m) - sm) + 7) & ~(size_t)7;
+  // [W] s + the basis vectors taken into it: zero on every pivot row.  Its syndrome
+  // part is zero iff s lies in the span of the kept columns, and its combination
+  // part then names the kept columns whose sum is s.
+  uint64_t* acc = (uint64_t*)(sm + acc_off);
   uint32_t* tk = (uint32_t*)(acc + W);                             // OSD-CS: [npad / 32] kept sorted positions
   // WIN: after the sort, keys holds npad u32 column indices followed by npad
   // per-position counts (then exclusive offsets) of newly touched rows
   int32_t* pcnt = (int32_t*)keys + a.npad;
-  __shared__ int s_job, s_r, s_ns, s_inc, s_inst;
+  __shared__ int s_job, s_r, s_done, s_inc, s_inst;
   __shared__ int s_pref[MAX_MULTI_OSD + 1];
   __shared__ uint64_t s_red;
   __shared__ unsigned long long s_best;     // OSD-CS: (order key of the soft weight, candidate rank)
@@ -216,30 +231,6 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
     if (first_job) return (int)blockIdx.x;
     if (total <= (int)gridDim.x) return total;
     return (int)gridDim.x + atomicAdd(MULTI ? mu.next : &a.counters[a.cnt_next], 1);
-  };
-  // acc = s + sum of the basis vectors pivoted on rows of s.  With a fully
-  // reduced basis this is zero on every pivot row; its syndrome part is zero iff
-  // s lies in the span of the kept columns, and its combination part then names
-  // the kept columns whose sum is s.  Returns nonzero iff the syndrome part is.
-  auto reduce_syndrome = [&]() {
-    __syncthreads();
-    if (tid < W) acc[tid] = 0ull;
-    __syncthreads();
-    for (int i = tid; i < s_ns; i += NT) {
-      const int row = srow[i];
-      atomicXor((unsigned long long*)&acc[row >> 6], (unsigned long long)(1ull << (row & 63)));
-      const int pi = prow[row];
-      if (pi >= 0) {
-        const uint64_t* b = B + (int64_t)pi * W;
-#pragma unroll
-        for (int w = 0; w < W; ++w)
-          if (b[w]) atomicXor((unsigned long long*)&acc[w], (unsigned long long)b[w]);
-      }
-    }
-    __syncthreads();
-    int nz = 0;
-    for (int w = tid; w < MW; w += NT) nz |= acc[w] != 0ull;
-    return __syncthreads_or(nz);
   };
   while (true) {
     if (tid == 0) {
@@ -276,20 +267,14 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
     const int64_t shot = a.shot0 + ls;
     const float* L = a.osd_llr + (int64_t)job * a.n;
     int n_loc = a.n, rank_loc = a.rank, n0 = a.n;
-    if (tid == 0) { s_r = 0; s_ns = 0; s_inc = 0; }
+    if (tid == 0) { s_r = 0; s_done = 0; s_inc = 0; }
+    if (tid < W) acc[tid] = !WIN && tid < a.mw ? a.synd[ls * a.mw + tid] : 0ull;
     __syncthreads();
     if constexpr (!WIN && !PFX) {
-      // 1. sort columns by (L_v, v); list the syndrome's rows
+      // 1. sort columns by (L_v, v)
       for (int r = tid; r < a.m; r += NT) prow[r] = -1;
       if (a.order > 0)
         for (int i = tid; i < (a.npad >> 5); i += NT) tk[i] = 0u;
-      for (int wd = tid; wd < a.mw; wd += NT) {
-        uint64_t x = a.synd[ls * a.mw + wd];
-        if (x) {
-          const int base = atomicAdd(&s_ns, __popcll(x));
-          for (int k = 0; x; ++k, x &= x - 1) srow[base + k] = wd * 64 + (__ffsll((unsigned long long)x) - 1);
-        }
-      }
       uint64_t x[KPT];
 #pragma unroll
       for (int r = 0; r < KPT; ++r) {
@@ -381,13 +366,6 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
         // the prefix of the order, on H's rows
         n_loc = n0;
         for (int r = tid; r < a.m; r += NT) prow[r] = -1;
-        for (int wd = tid; wd < a.mw; wd += NT) {
-          uint64_t y = a.synd[ls * a.mw + wd];
-          if (y) {
-            const int base = atomicAdd(&s_ns, __popcll(y));
-            for (int k = 0; y; ++k, y &= y - 1) srow[base + k] = wd * 64 + (__ffsll((unsigned long long)y) - 1);
-          }
-        }
         __syncthreads();
       } else {
       // 1c. first window position touching each row
@@ -446,7 +424,10 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
         for (; x; x &= x - 1) {
           const int r = wd * 64 + (__ffsll((unsigned long long)x) - 1);
           if (ld_l2(&fpos[r]) >= n_loc) s_inc = 1;
-          else srow[atomicAdd(&s_ns, 1)] = ld_l2(&lmap[r]);
+          else {
+            const int lr = ld_l2(&lmap[r]);
+            atomicXor((unsigned long long*)&acc[lr >> 6], (unsigned long long)(1ull << (lr & 63)));
+          }
         }
       }
       __syncthreads();
@@ -461,13 +442,17 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
       if constexpr (WIN) return ld_l2(&lmap[r]);
       else return r;
     };
-    // 2. information set, 256 sorted candidates per pass (one per thread)
-    for (int base = 0; base < (skip ? 0 : n_loc); base += NT) {
+    // 2. information set, 63 sorted candidates per wave and pass
+    constexpr bool EARLY = WIN || PFX;
+    const bool early = EARLY || a.order == 0;
+    for (int base = 0; base < (skip ? 0 : n_loc); base += 63 * (NT / 64)) {
       const int r_start = s_r;
       __syncthreads();           // every wave has read s_r before wave 0 advances it
-      if (r_start >= rank_loc) break;
-      const int idx = base + tid;
-      const int col = idx < n_loc ? ((BL || WIN || PFX) ? (int)((const uint32_t*)keys)[idx] : (int)(keys[idx] & 0xFFFFFFFFu)) : -1;
+      if (r_start >= rank_loc || s_done) break;
+      const int idx = base + 63 * wave + lane;
+      const int col = lane < 63 && idx < n_loc
+                          ? ((BL || WIN || PFX) ? (int)((const uint32_t*)keys)[idx] : (int)(keys[idx] & 0xFFFFFFFFu))
+                          : -1;
       uint64_t v[W];
 #pragma unroll
       for (int w = 0; w < W; ++w) v[w] = 0ull;
@@ -495,30 +480,30 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
         if (wave == q) {
           // phase 2: in-order pass over this wave's candidates whose syndrome
           // part is still nonzero (zero ones depend on earlier columns)
+          if (lane == 63) {
+#pragma unroll
+            for (int w = 0; w < W; ++w) v[w] = acc[w];
+          }
           int r = r_done;
           int mine = -1;      // pivot row of the basis vector this lane became
-          auto nz = [&]() {
+          auto nonzero = [&]() -> uint64_t {
             uint64_t o = 0ull;
 #pragma unroll
             for (int w = 0; w < MW; ++w) o |= v[w];
-            return o != 0ull && col >= 0;
+            return __ballot(o != 0ull);
           };
-          uint64_t live = __ballot(nz());
-          while (live && r < rank_loc) {
+          constexpr uint64_t SYND = 1ull << 63;
+          uint64_t nz = nonzero(), live = nz & ~SYND;
+          while (live && r < rank_loc && (!early || (nz & SYND))) {
             const int j = __ffsll((unsigned long long)live) - 1;
-            uint64_t b[W];
+            uint64_t b[MW];
 #pragma unroll
-            for (int w = 0; w < W; ++w) b[w] = bcast64(v[w], j);
+            for (int w = 0; w < MW; ++w) b[w] = bcast64(v[w], j);
             int p = -1;
 #pragma unroll
             for (int w = 0; w < MW; ++w)
               if (p < 0 && b[w]) p = w * 64 + (__ffsll((unsigned long long)b[w]) - 1);
-#pragma unroll
-            for (int w = 0; w < RW; ++w)
-              if (w == (r >> 6)) b[MW + w] ^= 1ull << (r & 63);   // the column itself
             if (lane == j) {
-#pragma unroll
-              for (int w = 0; w < W; ++w) v[w] = b[w];
               mine = p;
               pivot[r] = p;
               kept[r] = col;
@@ -527,31 +512,54 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
             }
             const uint64_t mask = (lane > j) ? 0ull - bit_of<MW, W>(v, p) : 0ull;
 #pragma unroll
-            for (int w = 0; w < W; ++w) v[w] ^= b[w] & mask;
+            for (int w = 0; w < MW; ++w) v[w] ^= b[w] & mask;
+#pragma unroll
+            for (int w = 0; w < RW; ++w) {
+              if (EARLY && 64 * w > r) break;
+              const uint64_t own = w == (r >> 6) ? 1ull << (r & 63) : 0ull;    // the column itself
+              if (lane == j) v[MW + w] ^= own;
+              v[MW + w] ^= bcast64(v[MW + w], j) & mask;
+            }
             ++r;
-            live = __ballot(lane > j && nz());
+            nz = nonzero();
+            live = nz & ~SYND & (~1ull << j);
           }
-          // make the new vectors fully reduced among themselves (latest first)
-          uint64_t piv_lanes = __ballot(mine >= 0);
-          while (piv_lanes) {
-            const int j = 63 - __clzll((long long)piv_lanes);
-            piv_lanes &= ~(1ull << j);
-            const int pj = __builtin_amdgcn_readlane(mine, j);
-            uint64_t b[W];
+          const bool done = early && !(nz & SYND);
+          if (lane == 63) {
 #pragma unroll
-            for (int w = 0; w < W; ++w) b[w] = bcast64(v[w], j);
-            const uint64_t mask = (mine >= 0 && lane < j) ? 0ull - bit_of<MW, W>(v, pj) : 0ull;
-#pragma unroll
-            for (int w = 0; w < W; ++w) v[w] ^= b[w] & mask;
+            for (int w = 0; w < W; ++w) acc[w] = v[w];
+            s_r = r;
+            if (done) s_done = 1;
           }
-          if (mine >= 0) {
-            const int i = prow[mine];
+          if (!done) {
+            // make the new vectors fully reduced among themselves (latest first)
+            uint64_t piv_lanes = __ballot(mine >= 0);
+            while (piv_lanes) {
+              const int j = 63 - __clzll((long long)piv_lanes);
+              piv_lanes &= ~(1ull << j);
+              const int pj = __builtin_amdgcn_readlane(mine, j);
+              const uint64_t mask = (mine >= 0 && lane < j) ? 0ull - bit_of<MW, W>(v, pj) : 0ull;
 #pragma unroll
-            for (int w = 0; w < W; ++w) B[(int64_t)i * W + w] = v[w];
+              for (int w = 0; w < MW; ++w) v[w] ^= bcast64(v[w], j) & mask;
+#pragma unroll
+              for (int w = 0; w < RW; ++w) {
+                if (EARLY && 64 * w >= r) break;
+                v[MW + w] ^= bcast64(v[MW + w], j) & mask;
+              }
+            }
+            if (mine >= 0) {
+              const int i = prow[mine];
+#pragma unroll
+              for (int w = 0; w < W; ++w) B[(int64_t)i * W + w] = v[w];
+            }
           }
-          if (lane == 0) s_r = r;
         }
         __syncthreads();
+        // Stop as soon as s lies in the span of the kept columns.  Columns of the
+        // full information set are independent, so s has exactly one
+        // representation over them; the one found here (zero on the columns not
+        // yet kept) is it, and the rest of the scan could only add zeros.
+        if (s_done) break;       // (uniform; the loop over base ends there too)
         const int r_new = s_r;
         if (r_new > r_done) {
           // older basis vectors: clear their bits at the new pivots
@@ -591,15 +599,13 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
         r_done = r_new;
         __syncthreads();
       }
-      // Stop as soon as s lies in the span of the kept columns.  Columns of the
-      // full information set are independent, so s has exactly one
-      // representation over them; the one found here (zero on the columns not
-      // yet kept) is it, and the rest of the scan could only add zeros.
-      if ((WIN || PFX || a.order == 0) && !reduce_syndrome()) break;
     }
-    // 3. solve: s reduced by the basis vectors pivoted on rows of s
+    // 3. the solution is in acc
+    __syncthreads();
     const int r = s_r;
-    const int unspanned = skip ? 1 : reduce_syndrome();
+    int left = skip ? 1 : 0;
+    for (int w = tid; w < MW; w += NT) left |= acc[w] != 0ull;
+    const int unspanned = __syncthreads_or(left);
     // WIN: a window that does not span s says nothing about H unless it is all of H
     const bool incomplete = unspanned && !whole;
     const int not_in_span = unspanned && whole;
