@@ -96,7 +96,8 @@ struct DecodeDevice {
   int32_t* rowmap = nullptr;        // windowed OSD: [grid][2][m] row tables (WIN_NONE between shots)
   int32_t* retry = nullptr;         // OSD jobs the sorted prefix did not settle
   size_t cap_queue = 0, cap_osd = 0, cap_llr = 0, cap_basis = 0, cap_synd = 0, cap_gstate = 0, cap_rowmap = 0;
-  size_t cap_retry = 0;
+  int32_t* sorted = nullptr;        // OSD-CS: columns in the order of their posteriors, by job
+  size_t cap_retry = 0, cap_sorted = 0;
 };
 
 __global__ void k_zero_words(uint64_t* p, int64_t n) {
@@ -655,7 +656,7 @@ void free_device(DecodeDevice* d) {
   hipFree(d->row_ptr); hipFree(d->col_idx); hipFree(d->col_ptr); hipFree(d->csc_row); hipFree(d->csc_edge);
   hipFree(d->lam); hipFree(d->obs_mask); hipFree(d->counters); hipFree(d->shards); hipFree(d->queue); hipFree(d->osd_queue);
   hipFree(d->osd_llr); hipFree(d->basis); hipFree(d->synd); hipFree(d->gstate); hipFree(d->init); hipFree(d->sign0);
-  hipFree(d->rowmap); hipFree(d->retry); hipFree(d->lone);
+  hipFree(d->rowmap); hipFree(d->retry); hipFree(d->sorted); hipFree(d->lone);
   for (auto& q : d->scheds) {
     hipFree(q.c); hipFree(q.v); hipFree(q.f);
     hipFree(q.pce); hipFree(q.pve); hipFree(q.vmap);
@@ -1336,13 +1337,14 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
   const int osd_rows = osd_win ? WIN_MAX_ROWS : D.rows;
   if (osd_win) npad = WIN_KEYS;
   // (+ the OSD-CS bitset of kept sorted positions after the accumulator)
-  size_t osd_lds = (size_t)npad * 8 + (size_t)osd_rank * 8 + (size_t)osd_rows * 4 + (size_t)W * 8 + 64 +
-                   (cfg.osd_order > 0 ? (size_t)npad / 8 + 16 : 0);
+  const size_t osd_lists = (size_t)osd_rank * 8 + (size_t)osd_rows * 4 + (size_t)W * 8 + 64 +
+                           (cfg.osd_order > 0 ? (size_t)npad / 8 + 16 : 0);
   // small DEMs keep the elimination basis in LDS as well (at least two workgroups
   // per CU); their sorted keys are stored as 32-bit column indices
   const size_t basis_bytes = (size_t)std::max(osd_rank, 1) * W * 8;
-  const bool osd_bl = !osd_win && osd_lds_basis_ok(mw, npad) && osd_lds - (size_t)npad * 4 + basis_bytes <= 80 * 1024;
-  if (osd_bl) osd_lds += basis_bytes - (size_t)npad * 4;
+  const bool osd_bl = !osd_win && osd_lds_basis_ok(mw, npad) && osd_lists + (size_t)npad * 4 + basis_bytes <= 80 * 1024;
+  // (dense with 256 threads: the order is in device memory)
+  const size_t osd_lds = osd_lists + (osd_bl ? (size_t)npad * 4 + basis_bytes : osd_win ? (size_t)npad * 8 : 0);
   // dense OSD-0 on a DEM wider than the prefix: prefix pass, then a full sort of the rest
   const int pfx_keys = osd_bl ? PFX_KEYS_WAVE : PFX_KEYS_WG;
   // the prefix holds at most pfx_keys - 1 columns, so at most that many pivots:
@@ -1407,6 +1409,10 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
                                          win2 ? (size_t)win1_grid * (64 * mw1) * W1 : 0}))) != TMCS_OK))
       return st;
     if ((osd_pfx || win2) && (st = grow(&d->retry, &d->cap_retry, (size_t)chunk)) != TMCS_OK) return st;
+    // OSD-CS weighs candidates by the posteriors, so the order goes beside them
+    if (!osd_win && !osd_bl && cfg.osd_order > 0 &&
+        (st = grow(&d->sorted, &d->cap_sorted, (size_t)chunk * (size_t)D.cols)) != TMCS_OK)
+      return st;
     if (osd_win) {
       const size_t n_map = (size_t)std::max(osd_grid, win2 ? win1_grid : 0) * 2 * (size_t)std::max(D.rows, 1);
       const int32_t* before = d->rowmap;
@@ -1514,6 +1520,7 @@ OSDArgs osd_args(const DecodePass& ps, uint64_t* pred, tmcs_decode_stats* stats,
   o.npad = ps.npad;
   o.rowmap = d->rowmap; o.win_rows = cfg.osd_window > 0 ? cfg.osd_window : WIN_MAX_ROWS;
   o.jobs = nullptr; o.cnt_total = 2; o.cnt_next = 3; o.retry = nullptr; o.order = cfg.osd_order;
+  o.sorted = cfg.osd_order > 0 ? d->sorted : (int32_t*)d->osd_llr;
   return o;
 }
 
@@ -1596,10 +1603,10 @@ tmcs_status decode_osd_launch(const DecodePass& ps, uint64_t* pred, tmcs_decode_
     if (st != TMCS_OK) return st;
     OSDArgs orr = o;
     orr.jobs = ps.d->retry; orr.cnt_total = 4; orr.cnt_next = 5;
-    return dispatch_osd(ps.mw, ps.npad / (ps.osd_bl ? 64 : OSD_THREADS), ps.osd_bl, orr, ps.osd_grid, ps.osd_lds,
+    return dispatch_osd(ps.mw, ps.npad / 64, ps.osd_bl, orr, ps.osd_grid, ps.osd_lds,
                         stream);
   }
-  return dispatch_osd(ps.mw, ps.npad / (ps.osd_bl ? 64 : OSD_THREADS), ps.osd_bl, o, ps.osd_grid, ps.osd_lds, stream);
+  return dispatch_osd(ps.mw, ps.npad / 64, ps.osd_bl, o, ps.osd_grid, ps.osd_lds, stream);
 }
 
 }  // namespace

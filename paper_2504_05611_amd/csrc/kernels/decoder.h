@@ -242,6 +242,7 @@ struct OSDArgs {
   int32_t cnt_total, cnt_next;   // counters[] holding the number of jobs and the next job
   int32_t* retry;            // PFX, and WIN's first window: jobs left open (counted in counters[4])
   int32_t order;             // > 0: OSD-CS of this order (dense variants only)
+  int32_t* sorted;           // [jobs][n] sorted column indices (dense, 256 threads), may be osd_llr's memory
 };
 
 // Several decode items' windowed OSD queues served by one launch (osd.hip).
@@ -262,7 +263,7 @@ tmcs_status launch_osd_win_multi(const OSDArgs& first, const OSDMulti& mu, int g
 tmcs_status launch_osd_win(const OSDArgs& a, int grid, size_t lds, hipStream_t s, int mw);
 // Dense OSD-0 on the npad - 1 smallest keys first (jobs the prefix does not settle go to a.retry).
 tmcs_status dispatch_osd_pfx(int mw, bool bl, const OSDArgs& a, int grid, size_t lds, hipStream_t s);
-// Dense OSD-0 (or OSD-CS) with a full sort of kpt keys per thread; bl: basis in LDS, one wave per shot.
+// Dense OSD-0 (or OSD-CS) with a full sort; bl: basis in LDS, one wave per shot with kpt keys per lane.
 tmcs_status dispatch_osd(int mw, int kpt, bool bl, const OSDArgs& a, int grid, size_t lds, hipStream_t s);
 // Whether the one-wave variant with its basis in LDS applies (small DEMs).
 bool osd_lds_basis_ok(int mw, int npad);

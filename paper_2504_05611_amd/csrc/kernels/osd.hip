@@ -57,13 +57,12 @@ __device__ __forceinline__ uint64_t bcast64(uint64_t x, int src) {
   return ((uint64_t)hi << 32) | lo;
 }
 
-// Bitonic sort of npad = OSD_THREADS * KPT 64-bit keys, ascending.  Thread t
+// Bitonic sort of npad = (threads) * KPT 64-bit keys, ascending.  Thread t
 // holds elements t*KPT .. t*KPT+KPT-1 in registers; partners within a thread are
 // compared in registers, partners within a wave via lane shuffles, and only the
-// strides that cross waves go through LDS (`keys`), which also receives the
-// sorted result.
-// IDX32: store only the low 32 bits (the column index) of the sorted keys.
-template <int KPT, bool IDX32 = false>
+// strides that cross waves go through LDS (`keys`), which also receives the low
+// 32 bits (the column indices) of the sorted keys.
+template <int KPT>
 __device__ __forceinline__ void bitonic_sort_regs(uint64_t (&x)[KPT], uint64_t* keys, int npad) {
   const int tid = threadIdx.x;
   for (int k = 2; k <= npad; k <<= 1) {
@@ -114,10 +113,39 @@ __device__ __forceinline__ void bitonic_sort_regs(uint64_t (&x)[KPT], uint64_t* 
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < KPT; ++r) {
-    if (IDX32) ((uint32_t*)keys)[tid * KPT + r] = (uint32_t)x[r];
-    else keys[tid * KPT + r] = x[r];
+    ((uint32_t*)keys)[tid * KPT + r] = (uint32_t)x[r];
   }
   __syncthreads();
+}
+
+// The (L_v, v) order of every job's columns, for the dense variants with 256
+// threads: row job of `out` gets the column indices.  In place of the posteriors
+// (out = llr) where nothing reads them afterwards.
+//
+// A kernel of its own: up to 16384 8-byte keys take 128 KB of LDS, which the
+// elimination then held for its whole length, one workgroup per compute unit and
+// mostly one wave of its four at work, and the keys' registers (252, with spills)
+// allowed no second one either.  OSD-CS of order 7 on 8192 shots of the BB
+// [[144,12,12]] memory experiment (1822 jobs): 36.0 ms with the sort inside, 17.5
+// without it and 1.8 here (16 waves sort a job, not 4).
+template <int KPT, int NT>
+__global__ void __launch_bounds__(NT) k_osd_sort(const float* llr, int32_t* out, int n, const int32_t* jobs,
+                                                 const int32_t* counters, int cnt_total) {
+  extern __shared__ __align__(8) unsigned char sm[];
+  uint64_t* keys = (uint64_t*)sm;                                  // [NT * KPT]
+  const int tid = threadIdx.x, total = counters[cnt_total];
+  for (int jn = (int)blockIdx.x; jn < total; jn += (int)gridDim.x) {
+    const int64_t row = (int64_t)(jobs ? jobs[jn] : jn) * n;
+    uint64_t x[KPT];
+#pragma unroll
+    for (int r = 0; r < KPT; ++r) {
+      const int i = r * NT + tid;
+      x[r] = i < n ? (((uint64_t)order_key(llr[row + i]) << 32) | (uint32_t)i) : ~0ull;
+    }
+    bitonic_sort_regs<KPT>(x, keys, NT * KPT);
+    for (int i = tid; i < n; i += NT) out[row + i] = ((const int32_t*)keys)[i];
+    __syncthreads();
+  }
 }
 
 // Bit p of a register-resident bit vector (p < 64 * MW).
@@ -177,18 +205,21 @@ __device__ __forceinline__ uint64_t bit_of(const uint64_t (&v)[W], int p) {
 // item's window has the same shape (npad = WIN_KEYS, 64 MW local rows), so the
 // LDS layout does not change.
 template <int MW, int RW, int KPT, bool BL, int NT, bool WIN = false, bool PFX = false, bool MULTI = false>
-__global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
+// (dense, 256 threads: three workgroups per compute unit where the vectors leave the registers for it)
+__global__ void __launch_bounds__(NT, !BL && !WIN && !PFX && MW <= 15 ? 3 : 1) k_osd(OSDArgs a, OSDMulti mu) {
   constexpr int W = MW + RW;
   static_assert(!(WIN && BL), "the window variant keeps its basis in HBM");
   static_assert(!(WIN && PFX), "one front end per variant");
   static_assert(!MULTI || WIN, "multi-item launches use the windowed variant");
+  constexpr bool SORTED = !BL && !WIN && !PFX;                     // the order comes from k_osd_sort
   extern __shared__ __align__(8) unsigned char sm[];
   // local capacity: rank and rows of the problem the elimination sees
   const int cap_r = WIN ? 64 * MW : a.rank;
   const int cap_m = WIN ? 64 * MW : a.m;
-  uint64_t* keys = (uint64_t*)sm;                                  // [npad] (BL, WIN: u32 column indices)
+  uint64_t* keys = (uint64_t*)sm;                                  // [npad] (BL, WIN: u32 column indices; SORTED: none)
   uint64_t* lbasis = BL ? (uint64_t*)((uint32_t*)sm + a.npad) : keys + a.npad;   // BL: [rank][W]
-  int32_t* pivot = (int32_t*)(BL ? lbasis + (size_t)a.rank * W : keys + a.npad);   // [rank] pivot row of basis i
+  // [rank] pivot row of basis i
+  int32_t* pivot = (int32_t*)(BL ? lbasis + (size_t)a.rank * W : SORTED ? keys : keys + a.npad);
   int32_t* kept = pivot + cap_r;                                   // [rank] column of basis i
   int32_t* prow = kept + cap_r;                                    // [m] basis index of a pivot row, or -1
   // (an offset from sm, not an integer cast, so that the compiler keeps LDS addressing)
@@ -270,18 +301,22 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
     if (tid == 0) { s_r = 0; s_done = 0; s_inc = 0; }
     if (tid < W) acc[tid] = !WIN && tid < a.mw ? a.synd[ls * a.mw + tid] : 0ull;
     __syncthreads();
+    const int32_t* order = SORTED ? a.sorted + (int64_t)job * a.n : nullptr;
     if constexpr (!WIN && !PFX) {
       // 1. sort columns by (L_v, v)
       for (int r = tid; r < a.m; r += NT) prow[r] = -1;
       if (a.order > 0)
         for (int i = tid; i < (a.npad >> 5); i += NT) tk[i] = 0u;
-      uint64_t x[KPT];
+      if constexpr (!SORTED) {
+        uint64_t x[KPT];
 #pragma unroll
-      for (int r = 0; r < KPT; ++r) {
-        const int i = tid * KPT + r;
-        x[r] = i < a.n ? (((uint64_t)order_key(L[i]) << 32) | (uint32_t)i) : ~0ull;
+        for (int r = 0; r < KPT; ++r) {
+          const int i = tid * KPT + r;
+          x[r] = i < a.n ? (((uint64_t)order_key(L[i]) << 32) | (uint32_t)i) : ~0ull;
+        }
+        bitonic_sort_regs<KPT>(x, keys, a.npad);
       }
-      bitonic_sort_regs<KPT, BL>(x, keys, a.npad);
+      __syncthreads();
     } else {
       __shared__ int s_hist[256];
       __shared__ int s_wsum[NT / 64];
@@ -360,7 +395,7 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
         const int i = tid * KPT + r;
         x[r] = i < n0 ? keys[i] : ~0ull;
       }
-      bitonic_sort_regs<KPT, true>(x, keys, a.npad);
+      bitonic_sort_regs<KPT>(x, keys, a.npad);
       const uint32_t* col32 = (const uint32_t*)keys;
       if constexpr (PFX) {
         // the prefix of the order, on H's rows
@@ -450,9 +485,7 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
       __syncthreads();           // every wave has read s_r before wave 0 advances it
       if (r_start >= rank_loc || s_done) break;
       const int idx = base + 63 * wave + lane;
-      const int col = lane < 63 && idx < n_loc
-                          ? ((BL || WIN || PFX) ? (int)((const uint32_t*)keys)[idx] : (int)(keys[idx] & 0xFFFFFFFFu))
-                          : -1;
+      const int col = lane < 63 && idx < n_loc ? (SORTED ? order[idx] : ((const int32_t*)keys)[idx]) : -1;
       uint64_t v[W];
 #pragma unroll
       for (int w = 0; w < W; ++w) v[w] = 0ull;
@@ -636,7 +669,7 @@ __global__ void __launch_bounds__(NT) k_osd(OSDArgs a, OSDMulti mu) {
         // a candidate sums L over e_S + rep(e_T) (kept columns in order of
         // selection) and then over e_T; the lightest wins, ties to the earlier.
         auto col_at = [&](int p) -> int {
-          return BL ? (int)((const uint32_t*)keys)[p] : (int)(keys[p] & 0xFFFFFFFFu);
+          return SORTED ? order[p] : ((const int32_t*)keys)[p];
         };
         auto weight = [&](int c1, int c2) -> float {
           uint64_t x[RW];
@@ -824,16 +857,27 @@ tmcs_status dispatch_osd_pfx(int mw, bool bl, const OSDArgs& a, int grid, size_t
   return fail(TMCS_EUNSUPPORTED, "OSD supports at most 2048 detectors in this build");
 }
 
-template <int MW>
-tmcs_status dispatch_kpt(int kpt, const OSDArgs& a, int grid, size_t lds, hipStream_t s) {
-  switch (kpt) {
-    case 1: return launch_osd<MW, MW, 1, false>(a, grid, lds, s);
-    case 2: return launch_osd<MW, MW, 2, false>(a, grid, lds, s);
-    case 4: return launch_osd<MW, MW, 4, false>(a, grid, lds, s);
-    case 8: return launch_osd<MW, MW, 8, false>(a, grid, lds, s);
-    case 16: return launch_osd<MW, MW, 16, false>(a, grid, lds, s);
-    case 32: return launch_osd<MW, MW, 32, false>(a, grid, lds, s);
-    case 64: return launch_osd<MW, MW, 64, false>(a, grid, lds, s);
+template <int KPT, int NT>
+tmcs_status launch_sort(const OSDArgs& a, int grid, hipStream_t s) {
+  auto k = k_osd_sort<KPT, NT>;
+  const size_t lds = (size_t)KPT * NT * 8;
+  if (lds > 64 * 1024 && hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    return fail(TMCS_EUNSUPPORTED, "OSD sort does not fit in LDS");
+  grid = resident_grid((const void*)k, NT, lds, grid);
+  TMCS_LAUNCH("k_osd_sort", k, dim3(grid), dim3(NT), lds, s, a.osd_llr, a.sorted, a.n, a.jobs, a.counters, a.cnt_total);
+  return hip_check(hipGetLastError(), "k_osd_sort launch");
+}
+
+tmcs_status dispatch_sort(const OSDArgs& a, hipStream_t s) {
+  const int grid = 1 << 14;                          // (cut to what is resident)
+  switch (a.npad) {
+    case 256: return launch_sort<1, 256>(a, grid, s);
+    case 512: return launch_sort<2, 256>(a, grid, s);
+    case 1024: return launch_sort<4, 256>(a, grid, s);
+    case 2048: return launch_sort<2, 1024>(a, grid, s);
+    case 4096: return launch_sort<4, 1024>(a, grid, s);
+    case 8192: return launch_sort<8, 1024>(a, grid, s);
+    case 16384: return launch_sort<16, 1024>(a, grid, s);
     default: return fail(TMCS_EUNSUPPORTED, "OSD sort size");
   }
 }
@@ -894,16 +938,18 @@ tmcs_status dispatch_osd(int mw, int kpt, bool bl, const OSDArgs& a, int grid, s
     if (mw <= 8) return dispatch_kpt_lds<8>(kpt, a, grid, lds, s);
     return fail(TMCS_EUNSUPPORTED, "OSD basis in LDS: too many detectors");
   }
-  if (mw <= 1) return dispatch_kpt<1>(kpt, a, grid, lds, s);
-  if (mw <= 2) return dispatch_kpt<2>(kpt, a, grid, lds, s);
-  if (mw <= 4) return dispatch_kpt<4>(kpt, a, grid, lds, s);
-  if (mw <= 5) return dispatch_kpt<5>(kpt, a, grid, lds, s);
-  if (mw <= 8) return dispatch_kpt<8>(kpt, a, grid, lds, s);
-  if (mw <= 12) return dispatch_kpt<12>(kpt, a, grid, lds, s);
-  if (mw <= 15) return dispatch_kpt<15>(kpt, a, grid, lds, s);
-  if (mw <= 18) return dispatch_kpt<18>(kpt, a, grid, lds, s);
-  if (mw <= 24) return dispatch_kpt<24>(kpt, a, grid, lds, s);
-  if (mw <= 32) return dispatch_kpt<32>(kpt, a, grid, lds, s);
+  const tmcs_status st = dispatch_sort(a, s);
+  if (st != TMCS_OK) return st;
+  if (mw <= 1) return launch_osd<1, 1, 1, false>(a, grid, lds, s);
+  if (mw <= 2) return launch_osd<2, 2, 1, false>(a, grid, lds, s);
+  if (mw <= 4) return launch_osd<4, 4, 1, false>(a, grid, lds, s);
+  if (mw <= 5) return launch_osd<5, 5, 1, false>(a, grid, lds, s);
+  if (mw <= 8) return launch_osd<8, 8, 1, false>(a, grid, lds, s);
+  if (mw <= 12) return launch_osd<12, 12, 1, false>(a, grid, lds, s);
+  if (mw <= 15) return launch_osd<15, 15, 1, false>(a, grid, lds, s);
+  if (mw <= 18) return launch_osd<18, 18, 1, false>(a, grid, lds, s);
+  if (mw <= 24) return launch_osd<24, 24, 1, false>(a, grid, lds, s);
+  if (mw <= 32) return launch_osd<32, 32, 1, false>(a, grid, lds, s);
   return fail(TMCS_EUNSUPPORTED, "OSD supports at most 2048 detectors in this build");
 }
 
