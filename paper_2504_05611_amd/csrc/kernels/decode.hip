@@ -1171,6 +1171,8 @@ struct DecodePass {
   bool stream = false;         // state streamed through LDS (bp_stream.hip)
   StreamSched ss;
   bool osd_win = false, osd_pfx = false, osd_bl = false;
+  bool win_mid = false;        // and a middle one between them (decode_osd_launch)
+  size_t win_mid_lds = 0;
   bool win2 = false;           // windowed: a smaller first window, then the full one on what it leaves open
   int npad = 0, pfx_keys = 0, pfx_rank = 0, osd_grid = 0, pfx_grid = 0, win1_grid = 0, win1_rows = 0;
   int win1_mw = 0;             // words of local rows of the first window (WIN_SMALL_MW or WIN_MID_MW)
@@ -1388,6 +1390,13 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
   const size_t win1_lds = (size_t)WIN_KEYS * 8 + (size_t)(64 * mw1) * 12 + (size_t)W1 * 8 + 64;
   const int win1_fit = std::max<int>(1, (int)((160 * 1024) / (win1_lds + 512)));
   const int win1_grid = std::max(1, cus * std::min(win1_fit, cfg.osd_per_cu > 0 ? cfg.osd_per_cu : 8));
+  // What a 512-row window leaves open goes through a 1024-row one before the full
+  // one (on the full one's grid, basis and row tables, which are larger): these
+  // are a few shots, so a workgroup's latency is all of it, and a pivot costs half
+  // there.  d = 21 CNOT, 4096 shots: the retries of
+  // 0.04 % of them took 4.0 ms in the full window and take 2.6 ms so.
+  ps.win_mid = win2 && mw1 == WIN_SMALL_MW && user_rows > WIN_MID_ROWS;
+  ps.win_mid_lds = (size_t)WIN_KEYS * 8 + (size_t)WIN_MID_ROWS * 12 + (size_t)(2 * WIN_MID_MW) * 8 + 64;
   ps.osd_win = osd_win; ps.osd_pfx = osd_pfx; ps.osd_bl = osd_bl; ps.win2 = win2;
   ps.npad = npad; ps.pfx_keys = pfx_keys; ps.pfx_rank = pfx_rank;
   ps.osd_grid = osd_grid; ps.pfx_grid = pfx_grid; ps.osd_lds = osd_lds; ps.pfx_lds = pfx_lds;
@@ -1408,7 +1417,7 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
                                          osd_pfx ? (size_t)pfx_grid * (size_t)std::max(pfx_rank, 1) * W_pfx : 0,
                                          win2 ? (size_t)win1_grid * (64 * mw1) * W1 : 0}))) != TMCS_OK))
       return st;
-    if ((osd_pfx || win2) && (st = grow(&d->retry, &d->cap_retry, (size_t)chunk)) != TMCS_OK) return st;
+    if ((osd_pfx || win2) && (st = grow(&d->retry, &d->cap_retry, (size_t)chunk * (ps.win_mid ? 2 : 1))) != TMCS_OK) return st;
     // OSD-CS weighs candidates by the posteriors, so the order goes beside them
     if (!osd_win && !osd_bl && cfg.osd_order > 0 &&
         (st = grow(&d->sorted, &d->cap_sorted, (size_t)chunk * (size_t)D.cols)) != TMCS_OK)
@@ -1519,7 +1528,7 @@ OSDArgs osd_args(const DecodePass& ps, uint64_t* pred, tmcs_decode_stats* stats,
   o.pred = pred; o.nobs = D.nobs; o.stats = stats; o.ehat = cfg.ehat_dev; o.flags = cfg.flags_dev;
   o.npad = ps.npad;
   o.rowmap = d->rowmap; o.win_rows = cfg.osd_window > 0 ? cfg.osd_window : WIN_MAX_ROWS;
-  o.jobs = nullptr; o.cnt_total = 2; o.cnt_next = 3; o.retry = nullptr; o.order = cfg.osd_order;
+  o.jobs = nullptr; o.cnt_total = 2; o.cnt_next = 3; o.retry = nullptr; o.cnt_retry = 4; o.order = cfg.osd_order;
   o.sorted = cfg.osd_order > 0 ? d->sorted : (int32_t*)d->osd_llr;
   return o;
 }
@@ -1592,6 +1601,13 @@ tmcs_status decode_osd_launch(const DecodePass& ps, uint64_t* pred, tmcs_decode_
     if (st != TMCS_OK) return st;
     OSDArgs o2 = o;
     o2.jobs = ps.d->retry; o2.cnt_total = 4; o2.cnt_next = 5;
+    if (ps.win_mid) {
+      OSDArgs om = o2;
+      om.retry = ps.d->retry + ps.chunk; om.cnt_retry = 6;
+      om.win_rows = WIN_MID_ROWS;
+      if ((st = launch_osd_win(om, ps.osd_grid, ps.win_mid_lds, stream, WIN_MID_MW)) != TMCS_OK) return st;
+      o2.jobs = om.retry; o2.cnt_total = 6; o2.cnt_next = 7;
+    }
     return launch_osd_win(o2, ps.osd_grid, ps.osd_lds, stream, WIN_MW);
   }
   if (ps.osd_pfx) {

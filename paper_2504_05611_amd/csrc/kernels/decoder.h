@@ -240,7 +240,8 @@ struct OSDArgs {
   int32_t win_rows;          // WIN: most local rows a window may hold (<= 64 * MW)
   const int32_t* jobs;       // nullable: job j is jobs[j] (a retry pass), else j
   int32_t cnt_total, cnt_next;   // counters[] holding the number of jobs and the next job
-  int32_t* retry;            // PFX, and WIN's first window: jobs left open (counted in counters[4])
+  int32_t* retry;            // PFX, and WIN's smaller windows: jobs left open
+  int32_t cnt_retry;         // counters[] holding their number
   int32_t order;             // > 0: OSD-CS of this order (dense variants only)
   int32_t* sorted;           // [jobs][n] sorted column indices (dense, 256 threads), may be osd_llr's memory
 };
@@ -259,7 +260,7 @@ struct OSDMulti {
 // for a first window (a.retry receives what it leaves open).
 tmcs_status launch_osd_win_multi(const OSDArgs& first, const OSDMulti& mu, int grid, size_t lds, hipStream_t s,
                                  int mw);
-// Windowed OSD-0 (DEMs beyond the dense limits).
+// Windowed OSD-0 (DEMs beyond the dense limits) with mw words of local rows.
 tmcs_status launch_osd_win(const OSDArgs& a, int grid, size_t lds, hipStream_t s, int mw);
 // Dense OSD-0 on the npad - 1 smallest keys first (jobs the prefix does not settle go to a.retry).
 tmcs_status dispatch_osd_pfx(int mw, bool bl, const OSDArgs& a, int grid, size_t lds, hipStream_t s);

@@ -656,7 +656,7 @@ __global__ void __launch_bounds__(NT, !BL && !WIN && !PFX && MW <= 15 ? 3 : 1) k
     if ((PFX || (WIN && a.retry)) && incomplete) {
       // PFX: the full sort decides this one; WIN with a retry list (the smaller
       // first window): the full window does
-      if (tid == 0) a.retry[atomicAdd(&a.counters[4], 1)] = job;
+      if (tid == 0) a.retry[atomicAdd(&a.counters[a.cnt_retry], 1)] = job;
       reset_rows();
       __syncthreads();
       continue;
