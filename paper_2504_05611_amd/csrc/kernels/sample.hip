@@ -41,7 +41,6 @@ namespace {
 
 constexpr int SB = 4096;          // shots per noise block
 constexpr int WPB = SB / 64;      // 64-shot words per block
-constexpr int FRAME_THREADS = 256;
 
 __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                               uint32_t k0, uint32_t k1, uint32_t out[4]) {
@@ -252,22 +251,27 @@ __device__ __forceinline__ int item_width(int32_t kind) {
 }
 
 // Operands of a thread's first PF items of one layer, loaded while the
-// previous layer runs.
-constexpr int PF = 4;
+// previous layer runs.  (Two, where a workgroup has 8 waves or more: a layer is
+// spread over more threads, and 52 instead of 86 registers let two workgroups of
+// 16 waves, or four of 8, share a compute unit.)
+template <int NT>
+constexpr int frame_pf() { return NT >= 512 ? 2 : 4; }
+template <int PF>
 struct FramePrefetch {
   int32_t v[PF][4];          // gate layers: the item's integers
   uint64_t ev[PF];           // noise layers: event words
 };
 
-template <int F>
-__device__ __forceinline__ void frame_prefetch(FramePrefetch& p, const FrameArgs& a, int L, const uint32_t* nl, int tid) {
+template <int F, int NT>
+__device__ __forceinline__ void frame_prefetch(FramePrefetch<frame_pf<NT>()>& p, const FrameArgs& a, int L, const uint32_t* nl, int tid) {
+  constexpr int PF = frame_pf<NT>();
   if (L >= a.nlayers) return;
   const int kind = a.layers[3 * L], cnt = a.layers[3 * L + 1], off = a.layers[3 * L + 2];
   if (kind == L_NOISE) {
     const uint32_t e0 = nl[2 * off], e1 = nl[2 * off + 1];
 #pragma unroll
     for (int j = 0; j < PF; ++j) {
-      const uint32_t e = e0 + tid + j * FRAME_THREADS;
+      const uint32_t e = e0 + tid + j * NT;
       if (e < e1) p.ev[j] = a.events[e];
     }
     return;
@@ -276,7 +280,7 @@ __device__ __forceinline__ void frame_prefetch(FramePrefetch& p, const FrameArgs
   const int32_t* it = a.data + off;
 #pragma unroll
   for (int j = 0; j < PF; ++j) {
-    const int g = (tid + j * FRAME_THREADS) / F;
+    const int g = (tid + j * NT) / F;
     if (g < cnt) {
 #pragma unroll
       for (int x = 0; x < 4; ++x)
@@ -288,10 +292,11 @@ __device__ __forceinline__ void frame_prefetch(FramePrefetch& p, const FrameArgs
 // One layer of the program on the F words of this workgroup.  Items of a layer
 // touch distinct frame words (noise events of one site may share a word, hence
 // the atomic XORs there; measurement records XOR into accumulator slots).
-template <int F>
-__device__ __forceinline__ void frame_layer(const FrameArgs& a, int L, const FramePrefetch& p, const uint32_t* nl,
+template <int F, int NT>
+__device__ __forceinline__ void frame_layer(const FrameArgs& a, int L, const FramePrefetch<frame_pf<NT>()>& p, const uint32_t* nl,
                                             uint64_t* fx, uint64_t* fz, uint64_t* slot, int64_t gw0, int64_t blk,
                                             int wib0, int tid) {
+  constexpr int PF = frame_pf<NT>();
   const int kind = a.layers[3 * L], cnt = a.layers[3 * L + 1], off = a.layers[3 * L + 2];
   if (kind == L_NOISE) {
     auto apply = [&](const uint64_t ev) {
@@ -318,10 +323,10 @@ __device__ __forceinline__ void frame_layer(const FrameArgs& a, int L, const Fra
     const uint32_t e0 = nl[2 * off], e1 = nl[2 * off + 1];
 #pragma unroll
     for (int j = 0; j < PF; ++j) {
-      const uint32_t e = e0 + tid + j * FRAME_THREADS;
+      const uint32_t e = e0 + tid + j * NT;
       if (e < e1) apply(p.ev[j]);
     }
-    for (uint32_t e = e0 + tid + PF * FRAME_THREADS; e < e1; e += FRAME_THREADS) apply(a.events[e]);
+    for (uint32_t e = e0 + tid + PF * NT; e < e1; e += NT) apply(a.events[e]);
     return;
   }
   const int w = item_width(kind);
@@ -375,10 +380,10 @@ __device__ __forceinline__ void frame_layer(const FrameArgs& a, int L, const Fra
   };
 #pragma unroll
   for (int j = 0; j < PF; ++j) {
-    const int i = tid + j * FRAME_THREADS;
+    const int i = tid + j * NT;
     if (i < cnt * F) item(i / F, i % F, p.v[j]);
   }
-  for (int i = tid + PF * FRAME_THREADS; i < cnt * F; i += FRAME_THREADS) {
+  for (int i = tid + PF * NT; i < cnt * F; i += NT) {
     const int g = i / F;
     int32_t v[4] = {0, 0, 0, 0};
     for (int x = 0; x < w; ++x) v[x] = it[w * g + x];
@@ -390,8 +395,8 @@ __device__ __forceinline__ void frame_layer(const FrameArgs& a, int L, const Fra
 // program runs with a barrier between layers; the next layer's operands are
 // loaded into registers while the current one runs (two register sets that
 // swap roles every layer).
-template <int F>
-__global__ void __launch_bounds__(FRAME_THREADS) k_frame(FrameArgs a) {
+template <int F, int NT>
+__global__ void __launch_bounds__(NT) k_frame(FrameArgs a) {
   extern __shared__ uint64_t smem[];
   uint64_t* fx = smem;
   uint64_t* fz = smem + (size_t)a.Q * F;
@@ -403,8 +408,8 @@ __global__ void __launch_bounds__(FRAME_THREADS) k_frame(FrameArgs a) {
   const int wib0 = (int)(gw0 - blk * WPB);                      // word-in-block of f = 0
   const int64_t ebase = (blk - a.blk0) * a.nsites;
   const int total = (2 * a.Q + a.nslots) * F;
-  for (int i = tid; i < total; i += FRAME_THREADS) smem[i] = 0ull;
-  for (int j = tid; j < a.nnoise; j += FRAME_THREADS) {
+  for (int i = tid; i < total; i += NT) smem[i] = 0ull;
+  for (int j = tid; j < a.nnoise; j += NT) {
     const int s0 = a.noise_s0[j], c = a.noise_cnt[j];
     uint32_t e0 = a.offsets[ebase + s0], e1 = a.offsets[ebase + s0 + c];
     e0 = e0 < a.capacity ? e0 : a.capacity;
@@ -413,21 +418,22 @@ __global__ void __launch_bounds__(FRAME_THREADS) k_frame(FrameArgs a) {
     nl[2 * j + 1] = e1;
   }
   __syncthreads();
-  FramePrefetch pa, pb;
-  frame_prefetch<F>(pa, a, 0, nl, tid);
+  FramePrefetch<frame_pf<NT>()> pa, pb;
+  frame_prefetch<F, NT>(pa, a, 0, nl, tid);
   for (int L = 0; L < a.nlayers; L += 2) {
-    frame_prefetch<F>(pb, a, L + 1, nl, tid);
-    frame_layer<F>(a, L, pa, nl, fx, fz, slot, gw0, blk, wib0, tid);
+    frame_prefetch<F, NT>(pb, a, L + 1, nl, tid);
+    frame_layer<F, NT>(a, L, pa, nl, fx, fz, slot, gw0, blk, wib0, tid);
     __syncthreads();
     if (L + 1 >= a.nlayers) break;
-    frame_prefetch<F>(pa, a, L + 2, nl, tid);
-    frame_layer<F>(a, L + 1, pb, nl, fx, fz, slot, gw0, blk, wib0, tid);
+    frame_prefetch<F, NT>(pa, a, L + 2, nl, tid);
+    frame_layer<F, NT>(a, L + 1, pb, nl, fx, fz, slot, gw0, blk, wib0, tid);
     __syncthreads();
   }
 }
 
 struct SampleDevice {
   int device = -1;
+  int cus = 1;                     // compute units of the device
   Program prog;
   int32_t* layers = nullptr;
   int32_t* data = nullptr;
@@ -469,6 +475,7 @@ void free_device(SampleDevice* d) {
 tmcs_status build_state(const Circuit& c, int dev, SampleDevice** out) {
   SampleDevice* d = new SampleDevice();
   d->device = dev;
+  if (hipDeviceGetAttribute(&d->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || d->cus < 1) d->cus = 1;
   tmcs_status st = compile_program(c, &d->prog);
   if (st != TMCS_OK) { delete d; return st; }
   std::vector<uint64_t> tabs(d->prog.tab_p.size() * SB);
@@ -557,23 +564,52 @@ tmcs_status grow(T** p, size_t* cap, size_t need) {
   return TMCS_OK;
 }
 
-int frame_words_per_wg(const Program& P, int Q, int nnoise, size_t* lds_bytes) {
+// Words of a workgroup's frames: as many as fit in 64 KB, but not so many that
+// compute units stay without a workgroup.  A layer is a barrier and a chain of
+// latencies whatever it holds, so more words cost little while there is nothing
+// else to run, and idle units cost everything: 16384 shots of the BB [[144,12,12]]
+// memory took 390 us with 8 words and 245 us with one.
+int frame_words_per_wg(const Program& P, int Q, int nnoise, int64_t words, int cus, size_t* lds_bytes) {
   const size_t per_word = (size_t)(2 * Q + P.nslots) * sizeof(uint64_t);
   const size_t fixed = (size_t)nnoise * 8;
   int F = 64;
-  while (F > 1 && per_word * F + fixed > 64 * 1024) F >>= 1;
+  while (F > 1 && (per_word * F + fixed > 64 * 1024 || words < (int64_t)F * cus)) F >>= 1;
   *lds_bytes = per_word * F + fixed;
   return F;
 }
 
-template <int F>
-tmcs_status launch_frame(const FrameArgs& a, int64_t nwg, size_t lds, hipStream_t s) {
+// Threads of a workgroup: about 16 waves per compute unit over the workgroups
+// resident there, and 16 waves for one-word frames of large circuits, where every
+// workgroup of a block goes through all the block's events.  Kernel time in us with
+// 256 / 512 / 1024 threads (256 with a prefetch of four, the others of two):
+//   one workgroup per unit    d = 21, 4096 shots 1885 / 1171 / 850; BB [[144,12,12]]
+//     memory, 65536 shots 339 / 252 / 232; d = 5 (few items), 4096 shots 123 / 108 / 122
+//   two                       BB [[144,12,12]] memory, 262144 shots 411 / 323 / 367
+//   four                      d = 9, 262144 shots 420 / 452 / 711
+//   one word, d = 21, 65536 shots                  3820 / 2440 / 2260
+int frame_threads(int F, int Q, int64_t nwg, int cus, size_t lds) {
+  const int64_t per_cu = std::min<int64_t>((nwg + cus - 1) / cus, (int64_t)(160 * 1024 / std::max<size_t>(lds, 1)));
+  if ((F == 1 || per_cu <= 1) && F * Q >= 640) return 1024;
+  return per_cu <= 3 ? 512 : 256;
+}
+
+template <int F, int NT>
+tmcs_status launch_frame_nt(const FrameArgs& a, int64_t nwg, size_t lds, hipStream_t s) {
+  auto k = k_frame<F, NT>;
   if (lds > 64 * 1024) {
-    if (hipFuncSetAttribute((const void*)k_frame<F>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
       return fail(TMCS_EUNSUPPORTED, "frame does not fit in LDS");
   }
-  TMCS_LAUNCH("k_frame", k_frame<F>, dim3((unsigned)nwg), dim3(FRAME_THREADS), lds, s, a);
+  TMCS_LAUNCH("k_frame", k, dim3((unsigned)nwg), dim3(NT), lds, s, a);
   return hip_check(hipGetLastError(), "k_frame launch");
+}
+
+template <int F>
+tmcs_status launch_frame(const FrameArgs& a, int64_t nwg, size_t lds, int cus, hipStream_t s) {
+  const int nt = frame_threads(F, a.Q, nwg, cus, lds);
+  if (nt == 1024) return launch_frame_nt<F, 1024>(a, nwg, lds, s);
+  if (nt == 512) return launch_frame_nt<F, 512>(a, nwg, lds, s);
+  return launch_frame_nt<F, 256>(a, nwg, lds, s);
 }
 
 // Scratch of the no-allocation sampler (tmcs_sample_noalloc): a file-scope
@@ -618,7 +654,8 @@ tmcs_status sample_run(const Circuit& c, uint64_t seed, uint32_t instance, uint6
   const int64_t stride = (int64_t)((n_shots + 63) / 64);
   const int64_t word_begin = (int64_t)(shot_begin / 64);
   size_t lds = 0;
-  const int F = frame_words_per_wg(P, c.num_qubits, d->nnoise, &lds);
+  const int64_t words = (int64_t)((shot_end + 63) / 64) - word_begin;
+  const int F = frame_words_per_wg(P, c.num_qubits, d->nnoise, words, d->cus, &lds);
   if (lds > 160 * 1024) return fail(TMCS_EUNSUPPORTED, "circuit frame exceeds the 160 KB LDS of one workgroup");
   // the overflow flag: per call, or a caller-owned sticky flag (graph replays)
   uint32_t* flag = overflow_out ? overflow_out : d->flag;
@@ -692,13 +729,13 @@ tmcs_status sample_run(const Circuit& c, uint64_t seed, uint32_t instance, uint6
     a.det_out = det; a.obs_out = obs; a.stride = stride;
     const int64_t nwg = (a.word_hi - a.wg_word0 + F - 1) / F;
     switch (F) {
-      case 64: st = launch_frame<64>(a, nwg, lds, stream); break;
-      case 32: st = launch_frame<32>(a, nwg, lds, stream); break;
-      case 16: st = launch_frame<16>(a, nwg, lds, stream); break;
-      case 8: st = launch_frame<8>(a, nwg, lds, stream); break;
-      case 4: st = launch_frame<4>(a, nwg, lds, stream); break;
-      case 2: st = launch_frame<2>(a, nwg, lds, stream); break;
-      default: st = launch_frame<1>(a, nwg, lds, stream); break;
+      case 64: st = launch_frame<64>(a, nwg, lds, d->cus, stream); break;
+      case 32: st = launch_frame<32>(a, nwg, lds, d->cus, stream); break;
+      case 16: st = launch_frame<16>(a, nwg, lds, d->cus, stream); break;
+      case 8: st = launch_frame<8>(a, nwg, lds, d->cus, stream); break;
+      case 4: st = launch_frame<4>(a, nwg, lds, d->cus, stream); break;
+      case 2: st = launch_frame<2>(a, nwg, lds, d->cus, stream); break;
+      default: st = launch_frame<1>(a, nwg, lds, d->cus, stream); break;
     }
     if (st != TMCS_OK) return st;
   }
