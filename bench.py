@@ -207,18 +207,21 @@ def lanes_state_bytes(dem):
 
 def roofline(kern, parts, workload):
     """Roofline of the dominant kernel.  parts: per decoded instance (dem, stats dict, shots);
-    k_bp (state in LDS): VALU lane-ops of the 10-op model; k_bp_dev and k_bp_lanes (state in
+    k_bp (state in LDS) and k_bp_stream (state streamed through LDS): VALU lane-ops of the
+    10-op model; k_bp_dev and k_bp_lanes (state in
     device memory): HBM bytes of the state read and written once per BP iteration."""
     dominant = max(kern.items(), key=lambda kv: kv[1][1])[0]
     launches, ms = kern[dominant]
     sec = ms / 1e3
     out = dict(kernel=dominant, avg_launch_ms=ms / launches, launches=launches)
-    if dominant == "k_bp":
-        ops = sum(BP_OPS_PER_EDGE_ITER * d.edges * st["bp_iters"] for d, st, _, gs in parts if not gs)
+    if dominant in ("k_bp", "k_bp_stream"):
+        streamed = dominant == "k_bp_stream"
+        ops = sum(BP_OPS_PER_EDGE_ITER * d.edges * st["bp_iters"] for d, st, _, gs in parts if bool(gs) == streamed)
         ach = ops / sec / 1e12
         out.update(bound="alu", achieved=ach, peak=VALU_PEAK_TOPS, unit="TOP/s", frac=ach / VALU_PEAK_TOPS,
                    model=f"{BP_OPS_PER_EDGE_ITER} lane-ops per edge per BP iteration, summed over the "
-                         f"instances whose BP state is in LDS ({ops:.4g} lane-ops in {launches} launches)")
+                         f"instances whose BP state is {'streamed through' if streamed else 'in'} LDS "
+                         f"({ops:.4g} lane-ops in {launches} launches)")
     elif dominant == "k_bp_lanes":
         byts = sum(2 * lanes_state_bytes(d) * st["bp_iters"] for d, st, _, gs in parts if gs)
         ach = byts / sec / 1e9
