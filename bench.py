@@ -216,7 +216,9 @@ def roofline(kern, parts, workload):
     out = dict(kernel=dominant, avg_launch_ms=ms / launches, launches=launches)
     if dominant in ("k_bp", "k_bp_stream"):
         streamed = dominant == "k_bp_stream"
-        ops = sum(BP_OPS_PER_EDGE_ITER * d.edges * st["bp_iters"] for d, st, _, gs in parts if bool(gs) == streamed)
+        # (one BP kernel for all of them, or those whose state is large and those whose state is not)
+        alone = not any(k in kern for k in ("k_bp", "k_bp_stream", "k_bp_dev", "k_bp_lanes") if k != dominant)
+        ops = sum(BP_OPS_PER_EDGE_ITER * d.edges * st["bp_iters"] for d, st, _, gs in parts if alone or bool(gs) == streamed)
         ach = ops / sec / 1e12
         out.update(bound="alu", achieved=ach, peak=VALU_PEAK_TOPS, unit="TOP/s", frac=ach / VALU_PEAK_TOPS,
                    model=f"{BP_OPS_PER_EDGE_ITER} lane-ops per edge per BP iteration, summed over the "
