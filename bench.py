@@ -53,20 +53,23 @@ EVENT_APPLY_OPS = 4
 # Commands and raw figures: profiles/hbm_traffic_*.md
 TRAFFIC = {
     "sc_nlcnot_mixed": {
-        # one multi-item launch per step (every instance whose BP state is in device memory)
-        "k_bp_dev": {"src": ['paper_2504_05611_amd/csrc/kernels/decode.hip',
-                             'paper_2504_05611_amd/csrc/kernels/decoder.h'],
-                     "sha256": "2b6a8f200bbd177d2567d627c8565e7a49121cb2faaa2885323da00ae7d0dfa5",
-                     "fetch_kib": 643348669.0, "write_kib": 270640247.1},
+        # one multi-item launch per step
+        "k_bp_stream": {"src": ['paper_2504_05611_amd/csrc/kernels/bp_stream.hip',
+                                'paper_2504_05611_amd/csrc/kernels/bp_stream.h',
+                                'paper_2504_05611_amd/csrc/kernels/bp_team.h'],
+                        "sha256": "0e04daa65d34d1df40f0edf623176e3fbe243634ff4e05b5903b881a023dbf5a",
+                        "fetch_kib": 83090383.8, "write_kib": 92561194.5},
     },
     "sc5_nlcnot": {
-        "k_bp": {"src": ['paper_2504_05611_amd/csrc/kernels/decode.hip',
-                         'paper_2504_05611_amd/csrc/kernels/decoder.h'],
-                 "sha256": "2b6a8f200bbd177d2567d627c8565e7a49121cb2faaa2885323da00ae7d0dfa5",
-                 "fetch_kib": 72902.9, "write_kib": 133817.9},
-        "k_frame": {"src": ['paper_2504_05611_amd/csrc/kernels/sample.hip', 'paper_2504_05611_amd/csrc/host/program.cpp'],
-                    "sha256": "00f029fb29532a447cb003e411236ebcd32b0891f81c819f6e0dbc44fb9670ad",
-                    "fetch_kib": 59909.7, "write_kib": 38549.7},
+        "k_bp": {"src": ['paper_2504_05611_amd/csrc/kernels/bp_chunk.hip',
+                         'paper_2504_05611_amd/csrc/kernels/bp_chunk.h',
+                         'paper_2504_05611_amd/csrc/kernels/bp_team.h'],
+                 "sha256": "d1309daaa562f45854b3cbe48d09c4fdf86aab692c95cd8be8768c84ff15757d",
+                 "fetch_kib": 45582.5, "write_kib": 115124.4},
+        "k_frame": {"src": ['paper_2504_05611_amd/csrc/kernels/sample.hip',
+                            'paper_2504_05611_amd/csrc/host/program.cpp'],
+                    "sha256": "80cb162d486ff4a927b96fd8c873057694403c61b958581820946205afd66834",
+                    "fetch_kib": 59886.8, "write_kib": 38549.5},
     },
 }
 FETCH_SCALE = 1048576.0 / 524302.5   # copy-kernel calibration (1 GiB read per launch)
