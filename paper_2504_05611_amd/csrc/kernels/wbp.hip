@@ -399,7 +399,7 @@ __global__ void __launch_bounds__(256) k_wbp_weights(const float* __restrict__ w
 // one accumulator).
 constexpr int SUM_RUN = 8;
 __global__ void __launch_bounds__(256) k_wbp_sum(const float* __restrict__ rows, int64_t TE, int64_t nshots,
-                                                 float* __restrict__ gw, bool exclusive) {
+                                                 float* gw) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= TE) return;
   float tot = 0.0f;
@@ -409,8 +409,7 @@ __global__ void __launch_bounds__(256) k_wbp_sum(const float* __restrict__ rows,
     for (int k = 0; k < SUM_RUN; ++k) x[k] = s0 + k < nshots ? rows[(s0 + k) * TE + i] : 0.0f;
     tot += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
   }
-  if (exclusive) gw[i] += tot;
-  else atomicAdd(&gw[i], tot);
+  atomicAdd(&gw[i], tot);
 }
 
 __global__ void k_wbp_transpose(const uint64_t* __restrict__ det, int32_t m, int64_t stride, int64_t nshots,
@@ -661,8 +660,7 @@ tmcs_status wbp_backward_run(const Dem& D, const float* w, int T, const uint64_t
     // small graphs: the shots are split too, so that the sum fills the GPU
     const int64_t bx = (TE + 255) / 256, runs = (a.shot1 - s0 + SUM_RUN - 1) / SUM_RUN;
     const int64_t by = std::max<int64_t>(1, std::min<int64_t>(runs, 2048 / std::max<int64_t>(bx, 1)));
-    TMCS_LAUNCH("k_wbp_sum", k_wbp_sum, dim3((unsigned)bx, (unsigned)by), dim3(256), 0, stream, d->rows, TE, a.shot1 - s0, gw,
-                by == 1);
+    TMCS_LAUNCH("k_wbp_sum", k_wbp_sum, dim3((unsigned)bx, (unsigned)by), dim3(256), 0, stream, d->rows, TE, a.shot1 - s0, gw);
     if ((st = hip_check(hipGetLastError(), "k_wbp_sum launch")) != TMCS_OK) return st;
   }
   return TMCS_OK;
