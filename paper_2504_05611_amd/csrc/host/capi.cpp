@@ -24,6 +24,15 @@ tmcs_status hip_check(hipError_t e, const char* what) {
   return e == hipErrorOutOfMemory ? TMCS_ENOMEM : TMCS_EDEVICE;
 }
 
+bool stream_capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
 }  // namespace tmcs
 
 using namespace tmcs;

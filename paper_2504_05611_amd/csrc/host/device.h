@@ -10,6 +10,8 @@
 namespace tmcs {
 
 tmcs_status hip_check(hipError_t e, const char* what);
+// Whether the stream is being captured into a graph.
+bool stream_capturing(hipStream_t stream);
 
 // sampler (sample.hip)
 // blk_off (device, nullable): added to every block index of the noise streams;

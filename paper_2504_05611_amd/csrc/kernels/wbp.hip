@@ -42,6 +42,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <mutex>
 #include <vector>
 
 #include "../host/device.h"
@@ -75,6 +76,8 @@ struct WbpDevice {
   size_t cap_wcol = 0;
   float* rows = nullptr;             // [shots of a round][T][E] dLoss/dw by shot
   size_t cap_rows = 0;
+  std::mutex mu;                     // held while a call sizes the scratch and enqueues its kernels
+  hipEvent_t last = nullptr;         // after the last kernel that used the scratch
 };
 
 bool g_force_gs = false;             // keep the state in device memory even when it fits in LDS
@@ -116,13 +119,14 @@ struct WbpArgs {
   float* llr;                // [T][n_shots][n]  (forward output)
   const float* gllr;         // [T][n_shots][n]  (backward input)
   float* rows;               // [shots][T][E]    (backward output)
+  float* gw;                 // [T][E]           (the same without rows: added to)
   const int32_t* gchk;       // [ngroups][64]
   const int32_t* gf;         // [ngroups]
   int32_t ngroups;
   const int32_t* vcol;       // [nvchunks][64]
   const int32_t* vrow;       // [nvchunks + 1]
   const int2* vce;           // [vrows][64]
-  const float* wcol;         // [T][vrows][64]
+  const float* wcol;         // [T][vrows][64] (forward, COL)
   int32_t nvchunks, vrows;
   unsigned char* ws;         // workspace
   Layout lay;
@@ -138,7 +142,8 @@ __device__ __forceinline__ uint32_t ld_sign(const uint32_t* p) {
 // (value, edge) pairs in order of value, then edge
 __device__ __forceinline__ bool before(float x, int32_t ex, float y, int32_t ey) { return x < y || (x == y && ex < ey); }
 
-template <bool GS>
+// COL: weights laid out by column record (a.wcol), else read from a.w by edge.
+template <bool GS, bool COL>
 __global__ void __launch_bounds__(1024) k_wbp_forward(WbpArgs a) {
   extern __shared__ __align__(8) unsigned char sm[];
   unsigned char* base = GS ? a.gstate + (int64_t)blockIdx.x * a.slab : sm;
@@ -240,7 +245,7 @@ __global__ void __launch_bounds__(1024) k_wbp_forward(WbpArgs a) {
       for (int64_t i = tid; i < nwords; i += NT) sg_out[i] = GS ? ld_sign(&es[i]) : es[i];
       // variable pass: L_t = lambda + sum_c m_t (checks ascending), a column to a
       // lane, COL_STEPS edges' records and weights in flight
-      const float* wt = a.wcol + (int64_t)(t - 1) * a.vrows * 64;
+      const float* wt = COL ? a.wcol + (int64_t)(t - 1) * a.vrows * 64 : a.w + (int64_t)(t - 1) * a.E;
       for (int g = wave; g < a.nvchunks; g += NW) {
         const int v = a.vcol[g * 64 + lane];
         const int row = a.vrow[g], K = a.vrow[g + 1] - row;
@@ -252,7 +257,7 @@ __global__ void __launch_bounds__(1024) k_wbp_forward(WbpArgs a) {
           for (int u = 0; u < COL_STEPS; ++u) {
             const int64_t at = (int64_t)(row + min(k0 + u, K - 1)) * 64 + lane;
             r[u] = a.vce[at];
-            ww[u] = wt[at];
+            ww[u] = COL ? wt[at] : wt[max(r[u].y, 0)];
           }
 #pragma unroll
           for (int u = 0; u < COL_STEPS; ++u) {
@@ -276,7 +281,8 @@ __global__ void __launch_bounds__(1024) k_wbp_forward(WbpArgs a) {
   }
 }
 
-template <bool GS>
+// ROWS: dLoss/dw by shot into a.rows, else added to a.gw.
+template <bool GS, bool ROWS>
 __global__ void __launch_bounds__(1024) k_wbp_backward(WbpArgs a) {
   extern __shared__ __align__(8) unsigned char sm[];
   unsigned char* base = GS ? a.gstate + (int64_t)blockIdx.x * a.slab : sm;
@@ -295,7 +301,7 @@ __global__ void __launch_bounds__(1024) k_wbp_backward(WbpArgs a) {
       const uint32_t* sg = (const uint32_t*)(rec + a.lay.state + a.lay.flags);
       const float* G = a.gllr + ((int64_t)(t - 1) * a.nshots + shot) * n;
       const float* w = a.w + (int64_t)(t - 1) * a.E;
-      float* row = a.rows + ((shot - a.shot0) * a.T + (t - 1)) * a.E;
+      float* row = ROWS ? a.rows + ((shot - a.shot0) * a.T + (t - 1)) * a.E : a.gw + (int64_t)(t - 1) * a.E;
       // gL_t(v) = G_t(v) + sum_c gq_t(v->c): two edges of each check, the next
       // iteration's argmins, carry any
       if constexpr (GS) {
@@ -362,7 +368,8 @@ __global__ void __launch_bounds__(1024) k_wbp_backward(WbpArgs a) {
             const float sigma = (sc ^ sp ^ se) ? -1.0f : 1.0f;
             const float mu = e == nag ? n2 : n1;
             const bool on = mu < WBP_BIG * 0.5f;           // (an empty minimum carries no gradient)
-            row[e] = on ? gm * sigma * mu : 0.0f;
+            if constexpr (ROWS) row[e] = on ? gm * sigma * mu : 0.0f;
+            else if (on) atomicAdd(&row[e], gm * sigma * mu);
             const float ce = on ? gm * we[u] * sigma : 0.0f;
             if (e == nag) acc2 += ce; else acc1 += ce;
           }
@@ -439,6 +446,7 @@ tmcs_status upload(T** dst, const std::vector<T>& v) {
 // The training kernels keep their own device copy of the graph (separate
 // from the decoder's) in a static map keyed by the DEM handle.
 struct Registry {
+  std::mutex mu;
   std::vector<std::pair<const Dem*, WbpDevice*>> items;
 };
 Registry g_reg;
@@ -446,6 +454,7 @@ Registry g_reg;
 tmcs_status ensure(const Dem& D, WbpDevice** out) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return fail(TMCS_EDEVICE, "no HIP device");
+  std::lock_guard<std::mutex> lock(g_reg.mu);
   for (auto& it : g_reg.items)
     if (it.first == &D && it.second->device == dev) { *out = it.second; return TMCS_OK; }
   WbpDevice* d = new WbpDevice();
@@ -505,19 +514,40 @@ tmcs_status ensure(const Dem& D, WbpDevice** out) {
   d->vrows = vrow.back();
   if ((st = upload(&d->gchk, gchk)) != TMCS_OK || (st = upload(&d->gf, gf)) != TMCS_OK ||
       (st = upload(&d->vcol, vcol)) != TMCS_OK || (st = upload(&d->vrow, vrow)) != TMCS_OK ||
-      (st = upload(&d->vce, vce)) != TMCS_OK)
+      (st = upload(&d->vce, vce)) != TMCS_OK ||
+      (st = hip_check(hipEventCreateWithFlags(&d->last, hipEventDisableTiming | hipEventDisableSystemFence), "hipEventCreate")) != TMCS_OK)
     return st;
   g_reg.items.push_back({&D, d});
   *out = d;
   return TMCS_OK;
 }
 
+// A call's turn at the handle's scratch (syndromes, laid-out weights, gradient
+// rows, slabs).  Calls may come from several threads and on several streams: each
+// one's kernels wait for those of the call before it, which costs an event per
+// call (2.6 us; with a system-scope fence, which only other devices and the host
+// need, 3.5).  A call that is being captured takes no turn, since its kernels run at
+// every replay, whatever else then does; it uses neither the laid-out weights nor
+// the rows (COL, ROWS), so replays only share what a forward pass always shared,
+// its syndromes.
+struct Turn {
+  WbpDevice* d;
+  hipStream_t stream;
+  std::lock_guard<std::mutex> lock;
+  bool captured;
+  tmcs_status st = TMCS_OK;
+  Turn(WbpDevice* d, hipStream_t stream) : d(d), stream(stream), lock(d->mu), captured(stream_capturing(stream)) {
+    if (!captured) st = hip_check(hipStreamWaitEvent(stream, d->last, 0), "wait for the last call on this DEM");
+  }
+  // Also after an error: kernels of the call may be on their way.
+  ~Turn() {
+    if (!captured) (void)hipEventRecord(d->last, stream);
+  }
+};
+
 // Device copy and arguments; the forward pass also needs the syndromes by shot.
-tmcs_status prepare(const Dem& D, int T, const uint64_t* det, uint64_t n_shots, WbpDevice** dd, WbpArgs* a,
+tmcs_status prepare(const Dem& D, int T, const uint64_t* det, uint64_t n_shots, WbpDevice* d, WbpArgs* a,
                     hipStream_t stream, bool forward) {
-  WbpDevice* d = nullptr;
-  tmcs_status st = ensure(D, &d);
-  if (st != TMCS_OK) return st;
   const int mw = std::max((D.rows + 63) / 64, 1);
   if (forward) {
     const size_t need = (size_t)n_shots * mw;
@@ -540,7 +570,6 @@ tmcs_status prepare(const Dem& D, int T, const uint64_t* det, uint64_t n_shots, 
   A.m = D.rows; A.n = D.cols; A.T = T; A.E = D.edges; A.nshots = (int64_t)n_shots;
   A.shot0 = 0; A.shot1 = (int64_t)n_shots;
   A.lay = layout(D, T);
-  *dd = d;
   return TMCS_OK;
 }
 
@@ -589,11 +618,14 @@ tmcs_status wbp_forward_run(const Dem& D, const float* w, int T, const uint64_t*
   if (ws_bytes < wbp_workspace_bytes(D, T, n_shots)) return fail(TMCS_EINVAL, "workspace too small");
   WbpDevice* d = nullptr;
   WbpArgs a{};
-  tmcs_status st = prepare(D, T, det, n_shots, &d, &a, stream, true);
+  tmcs_status st = ensure(D, &d);
   if (st != TMCS_OK) return st;
+  const Turn turn(d, stream);
+  if ((st = turn.st) != TMCS_OK || (st = prepare(D, T, det, n_shots, d, &a, stream, true)) != TMCS_OK) return st;
   a.w = w; a.llr = llr; a.ws = (unsigned char*)ws;
   const int64_t nwc = (int64_t)T * d->vrows * 64;
-  if (d->cap_wcol < (size_t)nwc) {
+  const bool col = !turn.captured;
+  if (col && d->cap_wcol < (size_t)nwc) {
     hipFree(d->wcol);
     d->wcol = nullptr;
     d->cap_wcol = 0;
@@ -601,7 +633,7 @@ tmcs_status wbp_forward_run(const Dem& D, const float* w, int T, const uint64_t*
     d->cap_wcol = (size_t)nwc;
   }
   a.wcol = d->wcol;
-  if (nwc)
+  if (col && nwc)
     TMCS_LAUNCH("k_wbp_weights", k_wbp_weights, dim3((unsigned)((d->vrows * 64 + 255) / 256), (unsigned)T), dim3(256), 0, stream,
                 w, D.edges, d->vce, (int64_t)d->vrows * 64, d->wcol);
   const int64_t nwords = (D.edges + 31) / 32;
@@ -610,13 +642,14 @@ tmcs_status wbp_forward_run(const Dem& D, const float* w, int T, const uint64_t*
   const int grid = grid_for(n_shots, threads);
   if (g_force_gs || lds > 160 * 1024) {
     if ((st = slabs(d, grid, lds, &a)) != TMCS_OK) return st;
-    TMCS_LAUNCH("k_wbp_forward", k_wbp_forward<true>, dim3(grid), dim3(threads), 0, stream, a);
+    auto k = col ? k_wbp_forward<true, true> : k_wbp_forward<true, false>;
+    TMCS_LAUNCH("k_wbp_forward", k, dim3(grid), dim3(threads), 0, stream, a);
     return hip_check(hipGetLastError(), "k_wbp_forward launch");
   }
-  if (lds > 64 * 1024 &&
-      hipFuncSetAttribute((const void*)k_wbp_forward<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+  auto k = col ? k_wbp_forward<false, true> : k_wbp_forward<false, false>;
+  if (lds > 64 * 1024 && hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
     return fail(TMCS_EUNSUPPORTED, "weighted BP state does not fit in LDS");
-  TMCS_LAUNCH("k_wbp_forward", k_wbp_forward<false>, dim3(grid), dim3(threads), lds, stream, a);
+  TMCS_LAUNCH("k_wbp_forward", k, dim3(grid), dim3(threads), lds, stream, a);
   return hip_check(hipGetLastError(), "k_wbp_forward launch");
 }
 
@@ -627,14 +660,18 @@ tmcs_status wbp_backward_run(const Dem& D, const float* w, int T, const uint64_t
   if (ws_bytes < wbp_workspace_bytes(D, T, n_shots)) return fail(TMCS_EINVAL, "workspace too small");
   WbpDevice* d = nullptr;
   WbpArgs a{};
-  tmcs_status st = prepare(D, T, det, n_shots, &d, &a, stream, false);
+  tmcs_status st = ensure(D, &d);
   if (st != TMCS_OK) return st;
-  a.w = w; a.gllr = gllr; a.ws = (unsigned char*)ws;
   const int64_t TE = (int64_t)T * D.edges;
   if (TE == 0) return TMCS_OK;
+  const Turn turn(d, stream);
+  if ((st = turn.st) != TMCS_OK || (st = prepare(D, T, det, n_shots, d, &a, stream, false)) != TMCS_OK) return st;
+  a.w = w; a.gllr = gllr; a.gw = gw; a.ws = (unsigned char*)ws;
   // rounds of shots whose rows fit ROWS_MAX
-  const int64_t round = std::max<int64_t>(1, std::min<int64_t>((int64_t)n_shots, (int64_t)(ROWS_MAX / 4) / TE));
-  if (d->cap_rows < (size_t)(round * TE)) {
+  const bool rows = !turn.captured;
+  const int64_t round = rows ? std::max<int64_t>(1, std::min<int64_t>((int64_t)n_shots, (int64_t)(ROWS_MAX / 4) / TE))
+                             : (int64_t)n_shots;
+  if (rows && d->cap_rows < (size_t)(round * TE)) {
     hipFree(d->rows);
     d->rows = nullptr;
     d->cap_rows = 0;
@@ -648,15 +685,17 @@ tmcs_status wbp_backward_run(const Dem& D, const float* w, int T, const uint64_t
   const int grid = grid_for((uint64_t)round, threads);
   const bool gs = g_force_gs || lds > 160 * 1024;
   if (gs && (st = slabs(d, grid, lds, &a)) != TMCS_OK) return st;
+  auto k = gs ? (rows ? k_wbp_backward<true, true> : k_wbp_backward<true, false>)
+              : (rows ? k_wbp_backward<false, true> : k_wbp_backward<false, false>);
   if (!gs && lds > 64 * 1024 &&
-      hipFuncSetAttribute((const void*)k_wbp_backward<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+      hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
     return fail(TMCS_EUNSUPPORTED, "weighted BP state does not fit in LDS");
   for (int64_t s0 = 0; s0 < (int64_t)n_shots; s0 += round) {
     a.shot0 = s0;
     a.shot1 = std::min<int64_t>((int64_t)n_shots, s0 + round);
-    if (gs) TMCS_LAUNCH("k_wbp_backward", k_wbp_backward<true>, dim3(grid), dim3(threads), 0, stream, a);
-    else TMCS_LAUNCH("k_wbp_backward", k_wbp_backward<false>, dim3(grid), dim3(threads), lds, stream, a);
+    TMCS_LAUNCH("k_wbp_backward", k, dim3(grid), dim3(threads), gs ? 0 : lds, stream, a);
     if ((st = hip_check(hipGetLastError(), "k_wbp_backward launch")) != TMCS_OK) return st;
+    if (!rows) continue;
     // small graphs: the shots are split too, so that the sum fills the GPU
     const int64_t bx = (TE + 255) / 256, runs = (a.shot1 - s0 + SUM_RUN - 1) / SUM_RUN;
     const int64_t by = std::max<int64_t>(1, std::min<int64_t>(runs, 2048 / std::max<int64_t>(bx, 1)));
@@ -667,12 +706,14 @@ tmcs_status wbp_backward_run(const Dem& D, const float* w, int T, const uint64_t
 }
 
 void wbp_release(const Dem& D) {
+  std::lock_guard<std::mutex> lock(g_reg.mu);
   for (size_t i = 0; i < g_reg.items.size(); ++i) {
     if (g_reg.items[i].first != &D) continue;
     WbpDevice* d = g_reg.items[i].second;
     hipFree(d->row_ptr); hipFree(d->col_idx); hipFree(d->col_ptr); hipFree(d->csc_row); hipFree(d->csc_edge);
     hipFree(d->lam); hipFree(d->synd); hipFree(d->gstate); hipFree(d->gchk); hipFree(d->gf); hipFree(d->rows);
     hipFree(d->vcol); hipFree(d->vrow); hipFree(d->vce); hipFree(d->wcol);
+    if (d->last) (void)hipEventDestroy(d->last);
     delete d;
     g_reg.items.erase(g_reg.items.begin() + i);
     --i;
