@@ -325,7 +325,18 @@ tmcs_status tmcs_count_errors(const uint64_t* pred_obs_dev, const uint64_t* obs_
  *  tmcs_wbp_forward: llr_dev receives FP32 [T][n_shots][cols], L_v after every
  *  iteration; the workspace keeps what the backward pass needs.
  *  tmcs_wbp_backward: given dLoss/dL as FP32 [T][n_shots][cols], accumulates
- *  dLoss/dw into grad_w_dev (FP32 [T][edges], caller zeroes it). */
+ *  dLoss/dw into grad_w_dev (FP32 [T][edges], caller zeroes it).
+ * Beside the workspace the DEM handle keeps device scratch that grows with the
+ * calls (growing it waits for the device) and is held until the handle is freed:
+ * 8 * ceil(rows / 64) bytes per shot for the syndromes, about 4 * T * edges bytes
+ * of laid-out weights, and for the backward pass one gradient row of 4 * T * edges
+ * bytes per shot, at most 4 GiB (more shots go in several rounds; fewer rows, or
+ * none, where the device has no room: slower, the same result to rounding).
+ * Calls on one handle may overlap, from several threads and on several streams:
+ * each one's kernels wait for those of the call before it.  A forward pass that is
+ * captured into a graph keeps its syndromes in the handle's scratch, so its replays
+ * must not overlap with other forward passes on that handle; captured passes use
+ * no rows and no laid-out weights. */
 tmcs_status tmcs_wbp_workspace_size(const tmcs_dem* d, int32_t T, uint64_t n_shots,
                                     size_t* bytes);
 tmcs_status tmcs_wbp_forward(const tmcs_dem* d, const float* weights_dev, int32_t T,

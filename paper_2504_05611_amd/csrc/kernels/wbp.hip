@@ -46,6 +46,7 @@
 #include <vector>
 
 #include "../host/device.h"
+#include "../host/scratch.h"
 #include "../host/timing.h"
 
 namespace tmcs {
@@ -76,6 +77,7 @@ struct WbpDevice {
   size_t cap_wcol = 0;
   float* rows = nullptr;             // [shots of a round][T][E] dLoss/dw by shot
   size_t cap_rows = 0;
+  size_t most_rows = ROWS_MAX / 4;   // floats of rows worth asking for (less once the device had no room)
   std::mutex mu;                     // held while a call sizes the scratch and enqueues its kernels
   hipEvent_t last = nullptr;         // after the last kernel that used the scratch
 };
@@ -624,13 +626,14 @@ tmcs_status wbp_forward_run(const Dem& D, const float* w, int T, const uint64_t*
   if ((st = turn.st) != TMCS_OK || (st = prepare(D, T, det, n_shots, d, &a, stream, true)) != TMCS_OK) return st;
   a.w = w; a.llr = llr; a.ws = (unsigned char*)ws;
   const int64_t nwc = (int64_t)T * d->vrows * 64;
-  const bool col = !turn.captured;
+  bool col = !turn.captured;
   if (col && d->cap_wcol < (size_t)nwc) {
     hipFree(d->wcol);
     d->wcol = nullptr;
     d->cap_wcol = 0;
-    if (hipMalloc((void**)&d->wcol, (size_t)nwc * sizeof(float)) != hipSuccess) return fail(TMCS_ENOMEM, "hipMalloc (wbp weights)");
-    d->cap_wcol = (size_t)nwc;
+    col = hipMalloc((void**)&d->wcol, (size_t)nwc * sizeof(float)) == hipSuccess;   // (no room: by edge)
+    if (col) d->cap_wcol = (size_t)nwc;
+    else { (void)hipGetLastError(); d->wcol = nullptr; }
   }
   a.wcol = d->wcol;
   if (col && nwc)
@@ -667,18 +670,25 @@ tmcs_status wbp_backward_run(const Dem& D, const float* w, int T, const uint64_t
   const Turn turn(d, stream);
   if ((st = turn.st) != TMCS_OK || (st = prepare(D, T, det, n_shots, d, &a, stream, false)) != TMCS_OK) return st;
   a.w = w; a.gllr = gllr; a.gw = gw; a.ws = (unsigned char*)ws;
-  // rounds of shots whose rows fit ROWS_MAX
-  const bool rows = !turn.captured;
-  const int64_t round = rows ? std::max<int64_t>(1, std::min<int64_t>((int64_t)n_shots, (int64_t)(ROWS_MAX / 4) / TE))
-                             : (int64_t)n_shots;
-  if (rows && d->cap_rows < (size_t)(round * TE)) {
+  // rounds of shots whose rows fit ROWS_MAX, or what the device has left; no rows at
+  // all where not even one shot's do
+  int64_t round = turn.captured ? 0 : std::min<int64_t>((int64_t)n_shots, (int64_t)(d->most_rows / (size_t)TE));
+  if (round > 0 && d->cap_rows < (size_t)(round * TE)) {
     hipFree(d->rows);
     d->rows = nullptr;
     d->cap_rows = 0;
-    if (hipMalloc((void**)&d->rows, (size_t)(round * TE) * sizeof(float)) != hipSuccess)
-      return fail(TMCS_ENOMEM, "hipMalloc (wbp gradient rows)");
-    d->cap_rows = (size_t)(round * TE);
+    const size_t got = alloc_most((size_t)round, 1, [&](size_t shots) {
+      if (hipMalloc((void**)&d->rows, shots * (size_t)TE * sizeof(float)) == hipSuccess) return true;
+      (void)hipGetLastError();
+      d->rows = nullptr;
+      return false;
+    });
+    if (got < (size_t)round) d->most_rows = got * (size_t)TE;
+    round = (int64_t)got;
+    d->cap_rows = got * (size_t)TE;
   }
+  const bool rows = round > 0;
+  if (!rows) round = (int64_t)n_shots;
   a.rows = d->rows;
   const size_t lds = (size_t)D.cols * 4 + (size_t)D.rows * 8 + 16;
   const int threads = threads_for(D);
