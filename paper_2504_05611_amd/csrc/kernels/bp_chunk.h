@@ -81,9 +81,12 @@ constexpr int CHUNK_PAD_ROWS = 8;
 // LDS bytes beyond the dynamic part (counters, histogram, job state).
 constexpr size_t CHUNK_LDS_STATIC = 1024;
 
-// Whether H fits the kernel's 16-bit state addresses and one compute unit's LDS
-// for every team size; *lds receives the bytes of one team of P lanes.
-bool chunk_fits(const Dem& D, int P, size_t* lds);
+// Whether a team of P lanes on this DEM fits in a compute unit's LDS.  The run
+// tables grow with the waves, so a DEM may fit for a few and not for sixteen.
+// *lds: the team's bytes; *usual: the same with tables of the usual length, which
+// is what the number of teams is chosen by before their size is known.
+bool chunk_fits(const Dem& D, int P, size_t* lds, size_t* usual);
+// TMCS_EUNSUPPORTED, without a message, where it does not fit.
 tmcs_status build_chunk_sched(const Dem& D, int P, ChunkSched* out);
 void free_chunk_sched(ChunkSched* s);
 // Lays out CSR-ordered weights w [T][E] by schedule step into wv and wc.

@@ -47,6 +47,7 @@
 #include <cmath>
 #include <cstring>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "../host/device.h"
@@ -59,9 +60,9 @@ namespace dec {
 
 namespace {
 
-constexpr int MAX_RUNS = 24;                // runs per wave and pass that the LDS estimate allows for
 constexpr int R_PART = 12;                   // column-pass record: part address << R_PART | j
 constexpr int HDR = 8;                      // table words per wave before the runs
+constexpr int USUAL_RUNS = 8;               // runs of a wave in both passes together, typically
 
 // Value of the lane whose index differs in bit `step`, for values that agree
 // within groups of `step` lanes (1, 2: swaps; 4, 8: mirrors of 8 and 16 lanes).
@@ -511,7 +512,7 @@ long assign_chunks(std::vector<Chunk>& ch, int NW, Cost cost, std::vector<std::v
     (*waves)[w].push_back(i);
     load[w] += cost(ch[i]);
   }
-  return *std::max_element(load.begin(), load.end());
+  return *std::max_element(load.begin(), load.end());   // (no chunks: 0)
 }
 
 std::vector<Chunk> column_chunks(const Dem& D) {
@@ -565,49 +566,65 @@ bool check_chunks(const Dem& D, int most, std::vector<Chunk>* out) {
   return true;
 }
 
-// The part size whose chunks take the team the fewest instructions, with a state of at most max_parts parts.
-bool best_check_chunks(const Dem& D, int NW, size_t max_parts, std::vector<Chunk>* best, std::vector<std::vector<int>>* waves) {
+// Runs of one width that a wave walks: {K, chunks | f << 16 (check pass)}.
+std::vector<std::pair<int32_t, int32_t>> wave_runs(const std::vector<int>& list, const std::vector<Chunk>& ch, bool check_pass) {
+  std::vector<std::pair<int32_t, int32_t>> runs;
+  for (size_t i = 0; i < list.size();) {
+    size_t k = i;
+    while (k < list.size() && k - i < 0xFFFF && ch[list[k]].K == ch[list[i]].K && ch[list[k]].f == ch[list[i]].f) ++k;
+    runs.push_back({ch[list[i]].K, (int32_t)(k - i) | (check_pass ? ch[list[i]].f << 16 : 0)});
+    i = k;
+  }
+  return runs;
+}
+
+// The chunks of a team of NW waves, which wave takes which, and its LDS bytes.
+struct ChunkPlan {
+  std::vector<Chunk> cc, vc;
+  std::vector<std::vector<int>> cw, vw;
+  size_t lds = 0;
+};
+
+size_t plan_lds(const ChunkPlan& p, int NW) {
+  ChunkSched s;
+  s.Ms = (int32_t)p.cc.size() * 64;
+  s.Ns = (int32_t)p.vc.size() * 64;
+  s.ntab = NW * HDR;
+  for (const auto& w : p.cw) s.ntab += 2 * (int32_t)wave_runs(w, p.cc, true).size();
+  for (const auto& w : p.vw) s.ntab += 2 * (int32_t)wave_runs(w, p.vc, false).size();
+  return s.lds();
+}
+
+// The plan whose check chunks take the team the fewest instructions, of those
+// that fit in one compute unit's LDS; false if none does.
+bool plan_chunks(const Dem& D, int NW, ChunkPlan* out) {
+  ChunkPlan p;
+  p.vc = column_chunks(D);
+  assign_chunks(p.vc, NW, chunk_cost_v, &p.vw);
   long best_cost = -1;
   for (int most : {PART_MAX_DEG, 20, 16, 12, 10, 8}) {
-    std::vector<Chunk> ch;
-    std::vector<std::vector<int>> wv;
-    if (!check_chunks(D, most, &ch) || ch.size() * 64 > max_parts) continue;
-    const long cost = ch.empty() ? 0 : assign_chunks(ch, NW, chunk_cost_c, &wv);
-    if (wv.empty()) wv.assign(NW, {});
+    if (!check_chunks(D, most, &p.cc)) continue;
+    const long cost = assign_chunks(p.cc, NW, chunk_cost_c, &p.cw);
+    p.lds = plan_lds(p, NW);
     // (a smaller part size also takes more state: at equal cost the larger one stays)
-    if (best_cost < 0 || cost < best_cost) {
-      best_cost = cost;
-      *best = ch;
-      *waves = wv;
-    }
+    if (p.lds + CHUNK_LDS_STATIC > 160 * 1024 || (best_cost >= 0 && cost >= best_cost)) continue;
+    best_cost = cost;
+    *out = p;
   }
   return best_cost >= 0;
 }
 
 }  // namespace
 
-namespace {
-// Column slots, and the check parts that fit beside them in one compute unit's LDS.
-size_t column_slots(const Dem& D) {
-  size_t cols = 0;
-  for (int v = 0; v < D.cols; ++v) cols += D.col_ptr[v + 1] > D.col_ptr[v];
-  return (cols + 63) / 64 * 64;
-}
-size_t max_parts(size_t Ns, int NW) {
-  const size_t rest = (Ns + 1) * 4 + (size_t)NW * (HDR + 2 * MAX_RUNS) * 4 + 28 + CHUNK_LDS_STATIC;
-  return rest < 160 * 1024 ? (160 * 1024 - rest) / 12 : 0;
-}
-}  // namespace
-
-bool chunk_fits(const Dem& D, int P, size_t* lds) {
-  std::vector<Chunk> cc;
-  std::vector<std::vector<int>> cw;
+bool chunk_fits(const Dem& D, int P, size_t* lds, size_t* usual) {
+  ChunkPlan p;
+  if (!plan_chunks(D, P / 64, &p)) return false;
   ChunkSched s;
-  s.Ns = (int32_t)column_slots(D);
-  if (!best_check_chunks(D, P / 64, max_parts((size_t)s.Ns, P / 64), &cc, &cw)) return false;
-  s.Ms = (int32_t)cc.size() * 64;
-  s.ntab = (int32_t)(P / 64 * (HDR + 16));
-  *lds = s.lds();
+  s.Ms = (int32_t)p.cc.size() * 64;
+  s.Ns = (int32_t)p.vc.size() * 64;
+  s.ntab = P / 64 * (HDR + 2 * USUAL_RUNS);
+  *lds = p.lds;
+  *usual = s.lds();
   return true;
 }
 
@@ -617,12 +634,10 @@ tmcs_status build_chunk_sched(const Dem& D, int P, ChunkSched* out) {
   s.P = P;
   std::vector<float> lam(D.cols);
   for (int v = 0; v < D.cols; ++v) lam[v] = (float)std::log((1.0 - D.priors[v]) / D.priors[v]);
-  std::vector<Chunk> cc, vc = column_chunks(D);
-  std::vector<std::vector<int>> cw, vw;
-  if (!best_check_chunks(D, NW, max_parts(column_slots(D), NW), &cc, &cw))
-    return fail(TMCS_EUNSUPPORTED, "BP state does not fit in LDS");
-  if (vc.empty()) vw.assign(NW, {});
-  else assign_chunks(vc, NW, chunk_cost_v, &vw);
+  ChunkPlan plan;
+  if (!plan_chunks(D, NW, &plan)) return TMCS_EUNSUPPORTED;   // (not an error of the call: no message)
+  const auto &cc = plan.cc, &vc = plan.vc;
+  const auto &cw = plan.cw, &vw = plan.vw;
   s.Ms = (int32_t)cc.size() * 64;
   s.Ns = (int32_t)vc.size() * 64;
   s.wide = (size_t)s.Ns * 4 > 0xFFFFu;
@@ -728,16 +743,12 @@ tmcs_status build_chunk_sched(const Dem& D, int P, ChunkSched* out) {
       const auto& list = pass ? cw[w] : vw[w];
       const auto& ch = pass ? cc : vc;
       tab[w * HDR + (pass ? 7 : 3)] = (int32_t)tab.size();
-      int n = 0;
-      for (size_t i = 0; i < list.size();) {
-        size_t k = i;
-        while (k < list.size() && k - i < 0xFFFF && ch[list[k]].K == ch[list[i]].K && ch[list[k]].f == ch[list[i]].f) ++k;
-        tab.push_back(ch[list[i]].K);
-        tab.push_back((int32_t)(k - i) | (pass ? ch[list[i]].f << 16 : 0));
-        ++n;
-        i = k;
+      const auto runs = wave_runs(list, ch, pass == 1);
+      for (const auto& r : runs) {
+        tab.push_back(r.first);
+        tab.push_back(r.second);
       }
-      tab[w * HDR + (pass ? 6 : 2)] = n;
+      tab[w * HDR + (pass ? 6 : 2)] = (int32_t)runs.size();
     }
   s.ntab = (int32_t)tab.size();
   // columns that flip an observable

@@ -80,6 +80,7 @@ struct DecodeDevice {
   std::vector<ChunkSched> chunks;   // schedules of the LDS-state kernel, one per team size used so far
   double log_start = 30.0;          // log10 of the largest magnitude BP starts from
   int64_t chunk_lds = 0;            // LDS bytes of a team, about (-1: the state does not fit)
+  std::vector<int> no_chunk;        // team sizes whose state and tables do not fit
   std::vector<StreamSched> streams; // schedules of the streaming kernel, one per team size used so far
   std::vector<int> no_stream;       // team sizes it does not take this DEM with
   float* cw = nullptr;              // per-edge weights by schedule step
@@ -1061,15 +1062,21 @@ tmcs_status get_psched(const Dem& D, DecodeDevice* d, int P, int mode, DecodeDev
   return TMCS_OK;
 }
 
-// Schedule of the LDS-state kernel for teams of P lanes, cached per P.
-tmcs_status get_chunk(const Dem& D, DecodeDevice* d, int P, ChunkSched* out) {
+// Schedule of the LDS-state kernel for teams of P lanes, cached per P; *ok:
+// whether it fits.
+tmcs_status get_chunk(const Dem& D, DecodeDevice* d, int P, bool* ok, ChunkSched* out) {
+  *ok = false;
   for (const auto& q : d->chunks)
-    if (q.P == P) { *out = q; return TMCS_OK; }
+    if (q.P == P) { *out = q; *ok = true; return TMCS_OK; }
+  for (int p : d->no_chunk)
+    if (p == P) return TMCS_OK;
   ChunkSched q;
   tmcs_status st = build_chunk_sched(D, P, &q);
+  if (st == TMCS_EUNSUPPORTED) { d->no_chunk.push_back(P); return TMCS_OK; }
   if (st != TMCS_OK) return st;
   d->chunks.push_back(q);
   *out = q;
+  *ok = true;
   return TMCS_OK;
 }
 
@@ -1242,14 +1249,17 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
   int chunk_P = -1, teams = 32;
   if (cfg.bp_global_state == 0) {
     if (d->chunk_lds == 0) {
-      size_t lds = 0;
-      d->chunk_lds = chunk_fits(D, 512, &lds) ? (int64_t)(lds + CHUNK_LDS_STATIC) : -1;
+      size_t lds = 0, usual = 0;
+      d->chunk_lds = chunk_fits(D, 512, &lds, &usual) ? (int64_t)(usual + CHUNK_LDS_STATIC) : -1;
     }
     if (d->chunk_lds > 0) {
       chunk_P = cfg.bp_threads > 0 ? std::min(1024, std::max(64, (cfg.bp_threads + 63) / 64 * 64))
                                    : chunk_team(D, lds_teams((size_t)d->chunk_lds, 64), n_shots, cus, &teams);
-      if ((st = get_chunk(D, d, chunk_P, &ps.cs)) != TMCS_OK) return st;
-      if (ps.cs.lds() + CHUNK_LDS_STATIC > 160 * 1024) chunk_P = -1;
+      // (a large team's tables may be what does not fit: then half the team)
+      bool ok = false;
+      while ((st = get_chunk(D, d, chunk_P, &ok, &ps.cs)) == TMCS_OK && !ok && chunk_P > 64) chunk_P = (chunk_P / 2 + 63) / 64 * 64;
+      if (st != TMCS_OK) return st;
+      if (!ok) chunk_P = -1;
     }
   }
   ps.inlds = chunk_P > 0;
