@@ -294,8 +294,12 @@ typedef struct {
  * the call does not wait for it.  The DEM handle keeps device scratch that grows
  * with the shots of a pass: about 4 * cols bytes per shot for the posteriors
  * handed to OSD (at most 8 GiB; decode_chunk caps it) plus a few words per shot.
- * Calls on one DEM handle share that scratch, so calls that may overlap in time
- * (different streams) need different handles. */
+ * The first call of a kind on a handle - another BP kernel or team size, which may
+ * follow from the number of shots - also builds its schedule: some milliseconds on
+ * the host and a copy that waits for none of the caller's work.  That may happen
+ * while the stream is being captured; scratch that has to grow for more shots must
+ * have grown before.  Calls on one DEM handle share the scratch, so calls that may
+ * overlap in time (different streams) need different handles. */
 tmcs_status tmcs_decode(const tmcs_dem* d, const tmcs_decoder_cfg* cfg,
                         const uint64_t* det_dev, uint64_t n_shots, uint64_t* pred_obs_dev,
                         tmcs_decode_stats* stats_dev, void* stream);

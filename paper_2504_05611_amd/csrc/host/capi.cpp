@@ -1,4 +1,5 @@
 // C ABI of the library: argument validation, handle ownership and errors.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -31,6 +32,21 @@ bool stream_capturing(hipStream_t stream) {
     return false;
   }
   return st != hipStreamCaptureStatusNone;
+}
+
+tmcs_status Uploader::copy(void** dst, const void* src, size_t bytes, size_t least) {
+  const std::string what = std::string(" failed (") + what_ + ")";
+  if (hipMalloc(dst, std::max(bytes, least)) != hipSuccess) return fail(TMCS_ENOMEM, "hipMalloc" + what);
+  if (bytes == 0) return TMCS_OK;
+  if ((!stream_ && hipStreamCreateWithFlags(&stream_, hipStreamNonBlocking) != hipSuccess) ||
+      hipMemcpyAsync(*dst, src, bytes, hipMemcpyHostToDevice, stream_) != hipSuccess ||
+      hipStreamSynchronize(stream_) != hipSuccess)
+    return fail(TMCS_EDEVICE, "copy" + what);
+  return TMCS_OK;
+}
+
+Uploader::~Uploader() {
+  if (stream_) (void)hipStreamDestroy(stream_);
 }
 
 }  // namespace tmcs

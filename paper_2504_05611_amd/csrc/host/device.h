@@ -13,6 +13,34 @@ tmcs_status hip_check(hipError_t e, const char* what);
 // Whether the stream is being captured into a graph.
 bool stream_capturing(hipStream_t stream);
 
+// While one lives, its thread may allocate although a stream is being captured.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  RelaxedCapture(const RelaxedCapture&) = delete;
+  RelaxedCapture& operator=(const RelaxedCapture&) = delete;
+};
+
+// Copies of host arrays in new device memory, for what a call finds it needs on its
+// way (a schedule for another team size).  They travel on a stream of their own:
+// they wait for no work of the caller's and stay out of a graph being captured.
+class Uploader {
+ public:
+  explicit Uploader(const char* what) : what_(what) {}
+  ~Uploader();
+  template <typename T>
+  tmcs_status operator()(T** dst, const std::vector<T>& v) {
+    return copy((void**)dst, v.data(), v.size() * sizeof(T), sizeof(T));
+  }
+
+ private:
+  tmcs_status copy(void** dst, const void* src, size_t bytes, size_t least);
+  RelaxedCapture relaxed_;
+  const char* what_;
+  hipStream_t stream_ = nullptr;
+};
+
 // sampler (sample.hip)
 // blk_off (device, nullable): added to every block index of the noise streams;
 // overflow_out (device, nullable): sticky event-buffer overflow flag owned by the

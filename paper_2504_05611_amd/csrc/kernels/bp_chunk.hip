@@ -477,15 +477,6 @@ __global__ void __launch_bounds__(256) k_chunk_weights(const float* __restrict__
 }
 
 // ------------------------------------------------------------------ host
-template <typename T>
-tmcs_status upload(T** dst, const std::vector<T>& v) {
-  const size_t bytes = std::max<size_t>(v.size(), 1) * sizeof(T);
-  if (hipMalloc((void**)dst, bytes) != hipSuccess) return fail(TMCS_ENOMEM, "hipMalloc failed (BP schedule)");
-  if (!v.empty() && hipMemcpy(*dst, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice) != hipSuccess)
-    return fail(TMCS_EDEVICE, "hipMemcpy failed (BP schedule)");
-  return TMCS_OK;
-}
-
 struct Chunk {
   int K = 0, f = 1;
   std::vector<int> item;   // [64] check part (c * 64 + part index is not needed: parts of a check are neighbours) or column; -1: empty
@@ -763,12 +754,13 @@ tmcs_status build_chunk_sched(const Dem& D, int P, ChunkSched* out) {
   std::vector<uint64_t> omask((size_t)D.obs_words * oc.size());
   for (size_t i = 0; i < oc.size(); ++i)
     for (int w = 0; w < D.obs_words; ++w) omask[(size_t)w * oc.size() + i] = D.obs_mask[(size_t)oc[i] * D.obs_words + w];
+  Uploader up("BP schedule");
   tmcs_status st;
-  if ((st = upload(&s.vrec, vrec)) != TMCS_OK || (st = upload(&s.crec, crec)) != TMCS_OK ||
-      (st = upload(&s.tab, tab)) != TMCS_OK || (st = upload(&s.lamp, lamp)) != TMCS_OK ||
-      (st = upload(&s.pinit, pinit)) != TMCS_OK || (st = upload(&s.vmap, vmap)) != TMCS_OK ||
-      (st = upload(&s.oslot, oslot)) != TMCS_OK || (st = upload(&s.omask, omask)) != TMCS_OK ||
-      (st = upload(&s.vedge, vedge)) != TMCS_OK || (st = upload(&s.cedge, cedge)) != TMCS_OK) {
+  if ((st = up(&s.vrec, vrec)) != TMCS_OK || (st = up(&s.crec, crec)) != TMCS_OK ||
+      (st = up(&s.tab, tab)) != TMCS_OK || (st = up(&s.lamp, lamp)) != TMCS_OK ||
+      (st = up(&s.pinit, pinit)) != TMCS_OK || (st = up(&s.vmap, vmap)) != TMCS_OK ||
+      (st = up(&s.oslot, oslot)) != TMCS_OK || (st = up(&s.omask, omask)) != TMCS_OK ||
+      (st = up(&s.vedge, vedge)) != TMCS_OK || (st = up(&s.cedge, cedge)) != TMCS_OK) {
     free_chunk_sched(&s);
     return st;
   }

@@ -392,18 +392,9 @@ __global__ void __launch_bounds__(1024, 8) k_bp_stream(StreamArgs, StreamMulti m
   if constexpr (!MULTI) flush();
 }
 
-// ------------------------------------------------------------------ host
-template <typename T>
-tmcs_status upload(T** dst, const std::vector<T>& v) {
-  const size_t bytes = std::max<size_t>(v.size(), 1) * sizeof(T);
-  if (hipMalloc((void**)dst, bytes) != hipSuccess) return fail(TMCS_ENOMEM, "hipMalloc failed (BP schedule)");
-  if (!v.empty() && hipMemcpy(*dst, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice) != hipSuccess)
-    return fail(TMCS_EDEVICE, "hipMemcpy failed (BP schedule)");
-  return TMCS_OK;
-}
-
 }  // namespace
 
+// ------------------------------------------------------------------ host
 tmcs_status build_stream_sched(const Dem& D, int P, StreamSched* out) {
   const tmcs_status no = TMCS_EUNSUPPORTED;   // (not an error of the call: no message)
   StreamSched s;
@@ -575,12 +566,13 @@ tmcs_status build_stream_sched(const Dem& D, int P, StreamSched* out) {
   std::vector<uint64_t> omask((size_t)D.obs_words * ocol.size());
   for (size_t i = 0; i < ocol.size(); ++i)
     for (int w = 0; w < D.obs_words; ++w) omask[(size_t)w * ocol.size() + i] = D.obs_mask[(size_t)ocol[i] * D.obs_words + w];
+  Uploader up("BP schedule");
   tmcs_status st;
-  if ((st = upload(&s.rec, rec)) != TMCS_OK || (st = upload(&s.desc, desc)) != TMCS_OK ||
-      (st = upload(&s.row0, row0)) != TMCS_OK || (st = upload(&s.pinit, pinit)) != TMCS_OK ||
-      (st = upload(&s.lamtab, lamtab)) != TMCS_OK || (st = upload(&s.lrec, lrec)) != TMCS_OK ||
-      (st = upload(&s.lamL, lamL)) != TMCS_OK || (st = upload(&s.vrec, vrec)) != TMCS_OK ||
-      (st = upload(&s.ocol, ocol)) != TMCS_OK || (st = upload(&s.omask, omask)) != TMCS_OK) {
+  if ((st = up(&s.rec, rec)) != TMCS_OK || (st = up(&s.desc, desc)) != TMCS_OK ||
+      (st = up(&s.row0, row0)) != TMCS_OK || (st = up(&s.pinit, pinit)) != TMCS_OK ||
+      (st = up(&s.lamtab, lamtab)) != TMCS_OK || (st = up(&s.lrec, lrec)) != TMCS_OK ||
+      (st = up(&s.lamL, lamL)) != TMCS_OK || (st = up(&s.vrec, vrec)) != TMCS_OK ||
+      (st = up(&s.ocol, ocol)) != TMCS_OK || (st = up(&s.omask, omask)) != TMCS_OK) {
     free_stream_sched(&s);
     return st;
   }

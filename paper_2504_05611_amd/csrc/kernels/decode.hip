@@ -99,6 +99,7 @@ struct DecodeDevice {
   size_t cap_queue = 0, cap_osd = 0, cap_llr = 0, cap_basis = 0, cap_synd = 0, cap_gstate = 0, cap_rowmap = 0;
   int32_t* sorted = nullptr;        // OSD-CS: columns in the order of their posteriors, by job
   size_t cap_retry = 0, cap_sorted = 0;
+  std::vector<void*> retired;      // scratch outgrown during a capture
 };
 
 __global__ void k_zero_words(uint64_t* p, int64_t n) {
@@ -653,6 +654,19 @@ tmcs_status grow(T** p, size_t* cap, size_t need) {
   return TMCS_OK;
 }
 
+// The same for scratch that only some of a handle's calls need, which a call being
+// captured may be the first to want.  Work in flight and earlier graphs may still use
+// what it then replaces: that is kept until the handle goes.
+template <typename T>
+tmcs_status grow_captured(DecodeDevice* d, T** p, size_t* cap, size_t need, hipStream_t stream) {
+  if (*cap >= need || !stream_capturing(stream)) return grow(p, cap, need);
+  const RelaxedCapture relaxed;
+  if (*p) d->retired.push_back(*p);
+  *p = nullptr;
+  *cap = 0;
+  return grow(p, cap, need);
+}
+
 void free_device(DecodeDevice* d) {
   hipFree(d->row_ptr); hipFree(d->col_idx); hipFree(d->col_ptr); hipFree(d->csc_row); hipFree(d->csc_edge);
   hipFree(d->lam); hipFree(d->obs_mask); hipFree(d->counters); hipFree(d->shards); hipFree(d->queue); hipFree(d->osd_queue);
@@ -666,6 +680,7 @@ void free_device(DecodeDevice* d) {
   for (auto& q : d->chunks) free_chunk_sched(&q);
   for (auto& q : d->streams) free_stream_sched(&q);
   hipFree(d->cw);
+  for (void* p : d->retired) hipFree(p);
   *d = DecodeDevice();
 }
 
@@ -863,8 +878,9 @@ tmcs_status get_sched(const Dem& D, DecodeDevice* d, int P, int mode, DecodeDevi
       }
   }
   tmcs_status st;
-  if ((st = upload(&q.c, cs)) != TMCS_OK) return st;
-  if ((st = upload(&q.v, vs)) != TMCS_OK) { hipFree(q.c); return st; }
+  Uploader up("BP schedule");
+  if ((st = up(&q.c, cs)) != TMCS_OK) return st;
+  if ((st = up(&q.v, vs)) != TMCS_OK) { hipFree(q.c); return st; }
   d->scheds.push_back(q);
   *out = q;
   return TMCS_OK;
@@ -910,7 +926,7 @@ tmcs_status get_fsched(const Dem& D, DecodeDevice* d, int P, int mode, DecodeDev
     fs[2 * i] = A;
     fs[2 * i + 1] = B;
   }
-  if ((st = upload(&q->f, fs)) != TMCS_OK) return st;
+  if ((st = Uploader("BP schedule")(&q->f, fs)) != TMCS_OK) return st;
   q->Kf = q->Kc;
   *out = *q;
   return TMCS_OK;
@@ -1049,10 +1065,11 @@ tmcs_status get_psched(const Dem& D, DecodeDevice* d, int P, int mode, DecodeDev
   pinit4[SINK] = make_int4(0, 0, -1, -1);                  // +0, +0, no argmin, every sign set
   if (vmap.empty()) vmap.push_back(-1);
   // (pc4 last: a schedule with pc4 set is complete)
-  if ((st = upload(&q->pv4, pv4)) != TMCS_OK || (st = upload(&q->pce, pce)) != TMCS_OK ||
-      (st = upload(&q->pve, pve)) != TMCS_OK || (st = upload(&q->vmap, vmap)) != TMCS_OK ||
-      (st = upload(&q->corig4, corig4)) != TMCS_OK || (st = upload(&q->pinit4, pinit4)) != TMCS_OK ||
-      (st = upload(&q->lamp, lamp)) != TMCS_OK || (st = upload(&q->pc4, pc4)) != TMCS_OK)
+  Uploader up("BP schedule");
+  if ((st = up(&q->pv4, pv4)) != TMCS_OK || (st = up(&q->pce, pce)) != TMCS_OK ||
+      (st = up(&q->pve, pve)) != TMCS_OK || (st = up(&q->vmap, vmap)) != TMCS_OK ||
+      (st = up(&q->corig4, corig4)) != TMCS_OK || (st = up(&q->pinit4, pinit4)) != TMCS_OK ||
+      (st = up(&q->lamp, lamp)) != TMCS_OK || (st = up(&q->pc4, pc4)) != TMCS_OK)
     return st;
   q->Mpk4 = Mpk4;
   q->Npk = Npk;
@@ -1323,7 +1340,8 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
     ps.bp_lds = ps.cs.lds();
     ps.bp_grid_max = cus * std::min(cfg.bp_per_cu > 0 ? cfg.bp_per_cu : teams, lds_teams(ps.bp_lds + CHUNK_LDS_STATIC, chunk_P));
     if (cfg.weights_dev &&
-        (st = grow(&d->cw, &d->cap_cw, ((size_t)std::max(cfg.max_iter, 1) * (ps.cs.vrows + ps.cs.crows) + CHUNK_PAD_ROWS) * 64)) != TMCS_OK)
+        (st = grow_captured(d, &d->cw, &d->cap_cw,
+                            ((size_t)std::max(cfg.max_iter, 1) * (ps.cs.vrows + ps.cs.crows) + CHUNK_PAD_ROWS) * 64, stream)) != TMCS_OK)
       return st;
   }
   if (ps.stream) {
@@ -1413,7 +1431,7 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
   ps.win1_grid = win1_grid; ps.win1_lds = win1_lds; ps.win1_rows = win1_rows; ps.win1_mw = mw1;
   if ((st = grow(&d->queue, &d->cap_queue, (size_t)chunk)) != TMCS_OK) return st;
   if ((st = grow(&d->synd, &d->cap_synd, (size_t)chunk * (size_t)std::max(mw, 1))) != TMCS_OK) return st;
-  if ((ps.stream || (ps.gstate && !ps.lanes)) && (st = grow(&d->gstate, &d->cap_gstate, (size_t)cus * per_cu * ps.team_bytes)) != TMCS_OK)
+  if ((ps.stream || (ps.gstate && !ps.lanes)) && (st = grow_captured(d, &d->gstate, &d->cap_gstate, (size_t)cus * per_cu * ps.team_bytes, stream)) != TMCS_OK)
     return st;
   if (ps.lanes && !shared_slab &&
       (st = grow(&d->gstate, &d->cap_gstate, (size_t)lanes_grid(ps.bp_grid_max, ps.team_bytes, chunk) * ps.team_bytes)) !=
@@ -1430,7 +1448,7 @@ tmcs_status decode_prepare(const Dem& D, const tmcs_decoder_cfg& cfg, uint64_t n
     if ((osd_pfx || win2) && (st = grow(&d->retry, &d->cap_retry, (size_t)chunk * (ps.win_mid ? 2 : 1))) != TMCS_OK) return st;
     // OSD-CS weighs candidates by the posteriors, so the order goes beside them
     if (!osd_win && !osd_bl && cfg.osd_order > 0 &&
-        (st = grow(&d->sorted, &d->cap_sorted, (size_t)chunk * (size_t)D.cols)) != TMCS_OK)
+        (st = grow_captured(d, &d->sorted, &d->cap_sorted, (size_t)chunk * (size_t)D.cols, stream)) != TMCS_OK)
       return st;
     if (osd_win) {
       const size_t n_map = (size_t)std::max(osd_grid, win2 ? win1_grid : 0) * 2 * (size_t)std::max(D.rows, 1);
