@@ -461,18 +461,20 @@ __global__ void __launch_bounds__(1024, 8) k_bp_chunk(ChunkArgs, ChunkMulti mu) 
   if constexpr (!MULTI) flush();
 }
 
-__global__ void __launch_bounds__(256) k_chunk_weights(const float* __restrict__ w, int64_t E,
+// (a grid has at most 65535 rows of blocks, and there may be more iterations)
+__global__ void __launch_bounds__(256) k_chunk_weights(const float* __restrict__ w, int64_t E, int T,
                                                        const int32_t* __restrict__ vedge, int64_t nv,
                                                        const int32_t* __restrict__ cedge, int64_t nc,
                                                        float* __restrict__ wv, float* __restrict__ wc) {
-  const int t = blockIdx.y;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nv) {
-    const int32_t e = vedge[i];
-    wv[t * nv + i] = e < 0 ? 0.0f : w[t * E + e];
-  } else if (i < nv + nc) {
-    const int32_t e = cedge[i - nv];
-    wc[t * nc + (i - nv)] = e < 0 ? 0.0f : w[t * E + e];
+  for (int t = blockIdx.y; t < T; t += gridDim.y) {
+    if (i < nv) {
+      const int32_t e = vedge[i];
+      wv[t * nv + i] = e < 0 ? 0.0f : w[t * E + e];
+    } else if (i < nv + nc) {
+      const int32_t e = cedge[i - nv];
+      wc[t * nc + (i - nv)] = e < 0 ? 0.0f : w[t * E + e];
+    }
   }
 }
 
@@ -778,8 +780,8 @@ tmcs_status launch_chunk_weights(const ChunkSched& s, const float* w, int T, int
                                  hipStream_t stream) {
   const int64_t nv = (int64_t)s.vrows * 64, nc = (int64_t)s.crows * 64;
   if (nv + nc == 0 || T < 1) return TMCS_OK;
-  TMCS_LAUNCH("k_chunk_weights", k_chunk_weights, dim3((unsigned)((nv + nc + 255) / 256), (unsigned)T), dim3(256), 0, stream,
-              w, E, s.vedge, nv, s.cedge, nc, wv, wc);
+  TMCS_LAUNCH("k_chunk_weights", k_chunk_weights, dim3((unsigned)((nv + nc + 255) / 256), (unsigned)std::min(T, 65535)), dim3(256), 0, stream,
+              w, E, T, s.vedge, nv, s.cedge, nc, wv, wc);
   return hip_check(hipGetLastError(), "k_chunk_weights launch");
 }
 

@@ -394,13 +394,14 @@ __global__ void __launch_bounds__(1024) k_wbp_backward(WbpArgs a) {
   }
 }
 
-// Weights in the order of the forward pass's column records.
-__global__ void __launch_bounds__(256) k_wbp_weights(const float* __restrict__ w, int64_t E, const int2* __restrict__ vce,
+// Weights in the order of the forward pass's column records (a grid has at most
+// 65535 rows of blocks, and there may be more iterations).
+__global__ void __launch_bounds__(256) k_wbp_weights(const float* __restrict__ w, int64_t E, int T, const int2* __restrict__ vce,
                                                      int64_t n, float* __restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const int32_t e = vce[i].y;
-  out[blockIdx.y * n + i] = e < 0 ? 0.0f : w[blockIdx.y * E + e];
+  for (int64_t t = blockIdx.y; t < T; t += gridDim.y) out[t * n + i] = e < 0 ? 0.0f : w[t * E + e];
 }
 
 // gw[i] += sum over shots of rows[shot][i]; blockIdx.y takes every gridDim.y-th
@@ -637,8 +638,8 @@ tmcs_status wbp_forward_run(const Dem& D, const float* w, int T, const uint64_t*
   }
   a.wcol = d->wcol;
   if (col && nwc)
-    TMCS_LAUNCH("k_wbp_weights", k_wbp_weights, dim3((unsigned)((d->vrows * 64 + 255) / 256), (unsigned)T), dim3(256), 0, stream,
-                w, D.edges, d->vce, (int64_t)d->vrows * 64, d->wcol);
+    TMCS_LAUNCH("k_wbp_weights", k_wbp_weights, dim3((unsigned)((d->vrows * 64 + 255) / 256), (unsigned)std::min(T, 65535)), dim3(256), 0, stream,
+                w, D.edges, T, d->vce, (int64_t)d->vrows * 64, d->wcol);
   const int64_t nwords = (D.edges + 31) / 32;
   const size_t lds = (size_t)D.cols * 4 + (size_t)D.rows * 13 + (size_t)nwords * 4 + 16;
   const int threads = threads_for(D);
