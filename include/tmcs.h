@@ -362,9 +362,9 @@ tmcs_status tmcs_wbp_global_state(int32_t on);
  * workgroups per compute unit, OSD workgroups per compute unit, BP lane
  * schedule - and writes the fastest into cfg's launch fields (the other fields
  * are kept).  Decoder output never depends on these fields.  The choice is
- * cached per (GPU architecture and CU count, DEM shape, decoder settings) for
- * the life of the process: a later call with the same key returns it without
- * decoding.  Synchronises the stream (when it decodes). */
+ * cached per (GPU architecture and CU count, DEM shape, decoder settings, shots
+ * per compute unit to a power of two) for the life of the process: a later call
+ * with the same key returns it without decoding.  Synchronises the stream (when it decodes). */
 tmcs_status tmcs_autotune(const tmcs_dem* d, const uint64_t* det_dev, uint64_t n_shots,
                           tmcs_decoder_cfg* cfg, void* stream);
 

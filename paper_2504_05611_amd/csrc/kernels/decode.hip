@@ -2047,17 +2047,21 @@ tmcs_status count_errors_async(const uint64_t* pred, const uint64_t* obs, uint32
 
 // Launch-shape search: decode the caller's syndromes with every candidate shape
 // and keep the fastest.  Results never depend on the launch shape, only time.
-// The autotuner's choices, cached per (GPU, DEM shape, decoder settings):
-// a later call with the same key returns the cached launch fields at once.
+// The autotuner's choices, cached per (GPU, DEM shape, decoder settings, shots per
+// compute unit to a power of two): a later call with the same key returns the
+// cached launch fields at once.  The shots and alpha are part of it because the
+// best team size follows from the shots a unit gets and the BP kernel from both.
 struct TuneKey {
   std::string arch;
   int rows, cols, rank, obs;
   int64_t edges;
-  int max_iter, use_osd, osd_order, osd_window, weighted, global_state;
+  int max_iter, use_osd, osd_order, osd_window, weighted, global_state, shots_log2;
+  uint32_t alpha_bits;
   bool operator<(const TuneKey& o) const {
-    return std::tie(arch, rows, cols, rank, obs, edges, max_iter, use_osd, osd_order, osd_window, weighted, global_state) <
+    return std::tie(arch, rows, cols, rank, obs, edges, max_iter, use_osd, osd_order, osd_window, weighted, global_state,
+                    shots_log2, alpha_bits) <
            std::tie(o.arch, o.rows, o.cols, o.rank, o.obs, o.edges, o.max_iter, o.use_osd, o.osd_order, o.osd_window,
-                    o.weighted, o.global_state);
+                    o.weighted, o.global_state, o.shots_log2, o.alpha_bits);
   }
 };
 struct TuneVal { int bp_threads, bp_per_cu, osd_per_cu, bp_sched; };
@@ -2071,9 +2075,14 @@ tmcs_status autotune_run(const Dem& D, const uint64_t* det, uint64_t n_shots, tm
   hipDeviceProp_t prop;
   if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess)
     return fail(TMCS_EDEVICE, "no HIP device");
+  // (beyond 1024 shots per unit every shape runs at its full rate)
+  int shots_log2 = 0;
+  for (uint64_t s = n_shots / (uint64_t)std::max(prop.multiProcessorCount, 1); s > 0 && shots_log2 < 11; s >>= 1) ++shots_log2;
+  uint32_t alpha_bits = 0;
+  std::memcpy(&alpha_bits, &cfg->alpha, sizeof alpha_bits);
   const TuneKey key{std::string(prop.gcnArchName) + "/" + std::to_string(prop.multiProcessorCount), D.rows, D.cols,
                     D.rank, D.nobs, D.edges, cfg->max_iter, cfg->use_osd, cfg->osd_order, cfg->osd_window,
-                    cfg->weights_dev != nullptr, cfg->bp_global_state};
+                    cfg->weights_dev != nullptr, cfg->bp_global_state, shots_log2, alpha_bits};
   {
     std::lock_guard<std::mutex> lock(g_tune_mu);
     auto it = g_tune_cache.find(key);
