@@ -254,7 +254,9 @@ typedef struct {
                                otherwise a positive multiple of 64 that caps it.  Results
                                never depend on it (each pass ends on its slowest shots, so
                                fewer passes are faster) */
-  int32_t bp_sched;         /* how a BP team's lanes share checks and columns (launch shape;
+  int32_t bp_sched;         /* how a BP team's lanes share checks and columns where its state
+                               is in device memory (launch shape; the kernels with their
+                               state in LDS, or streamed through it, have one schedule;
                                results never depend on it): 0 = library default, 1 =
                                longest-processing-time lists, 2 = strided (lane l of P takes
                                items l, l + P, ...: the lanes of a wave touch consecutive

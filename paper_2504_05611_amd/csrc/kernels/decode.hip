@@ -2116,6 +2116,9 @@ tmcs_status autotune_run(const Dem& D, const uint64_t* det, uint64_t n_shots, tm
         for (int sm : sched) {
         tmcs_decoder_cfg c = base;
         c.bp_threads = th; c.bp_per_cu = bc; c.osd_per_cu = oc; c.bp_sched = sm;
+        DecodePass ps;
+        if ((st = decode_prepare(D, c, n_shots, nullptr, stream, &ps)) != TMCS_OK) break;
+        if (sm != sched[0] && !ps.gstate) continue;   // (the other kernels have one schedule per team size)
         if ((st = decode_run(D, c, det, n_shots, pred, nullptr, stream)) != TMCS_OK) break;   // warm
         (void)hipEventRecord(e0, stream);
         if ((st = decode_run(D, c, det, n_shots, pred, nullptr, stream)) != TMCS_OK) break;
