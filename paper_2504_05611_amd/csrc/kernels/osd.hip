@@ -8,8 +8,8 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <tuple>
 #include <type_traits>
-#include <utility>
 
 #include "../host/device.h"
 #include "../host/timing.h"
@@ -872,15 +872,19 @@ __global__ void __launch_bounds__(NT, !BL && !WIN && !PFX && MW <= 15 ? 3 : 1) k
 // first job when the others are done.
 int resident_grid(const void* kernel, int threads, size_t lds, int grid) {
   static std::mutex mu;
-  static std::map<std::pair<const void*, size_t>, int> known;
+  static std::map<std::tuple<int, const void*, size_t>, int> known;
+  int dev = 0;
+  hipGetDevice(&dev);
   std::lock_guard<std::mutex> lock(mu);
-  auto it = known.find({kernel, lds});
+  auto it = known.find({dev, kernel, lds});
   if (it == known.end()) {
-    int dev = 0, cus = 0, per_cu = 0;
-    hipGetDevice(&dev);
+    int cus = 0, per_cu = 0;
     hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds) != hipSuccess || per_cu < 1) per_cu = 1 << 10;
-    it = known.emplace(std::make_pair(kernel, lds), std::max(1, cus) * per_cu).first;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds) != hipSuccess || per_cu < 1) {
+      (void)hipGetLastError();
+      per_cu = 1 << 10;
+    }
+    it = known.emplace(std::make_tuple(dev, kernel, lds), std::max(1, cus) * per_cu).first;
   }
   return std::max(1, std::min(grid, it->second));
 }
