@@ -77,8 +77,8 @@ WRITE_SCALE = 1048576.0 / 1048576.0
 
 WEIGHTS_DIR = os.path.join(ROOT, "paper_2504_05611_amd", "weights")
 SAMPLE_KERNELS = ("k_event", "k_scan", "k_frame", "k_zero_u32")
-DECODE_KERNELS = ("k_bp", "k_bp_stream", "k_bp_dev", "k_bp_lanes", "k_osd", "k_osd_retry", "k_compact", "k_begin_pass",
-                  "k_finish_stats", "k_chunk_weights", "k_zero_i32", "k_synd_transpose", "k_zero_words", "k_fill_i32")
+DECODE_KERNELS = ("k_bp", "k_bp_stream", "k_bp_dev", "k_bp_lanes", "k_osd", "k_osd_sort", "k_osd_retry", "k_compact",
+                  "k_begin_pass", "k_finish_stats", "k_chunk_weights", "k_zero_i32", "k_synd_transpose", "k_zero_words", "k_fill_i32")
 
 
 def traffic_bytes(workload, kernel):

@@ -48,3 +48,20 @@ def test_device_state_roofline_counts_state_once_per_iteration():
     assert r["avg_launch_ms"] == pytest.approx(2.0) and r["launches"] == 4
     assert r["achieved"] == pytest.approx(byts / 8e-3 / 1e9)
     assert r["frac"] == pytest.approx(r["achieved"] / 8000.0)
+
+
+def test_every_kernel_counts_towards_sampling_or_decoding():
+    """The names the library times its launches under, by the file they are launched in."""
+    import re
+    kernels = os.path.join(ROOT, "paper_2504_05611_amd", "csrc", "kernels")
+    names = {}
+    for f in sorted(os.listdir(kernels)):
+        text = open(os.path.join(kernels, f)).read()
+        names[f] = set(n for call in re.findall(r"TMCS_LAUNCH\(([^;{]*?), *[(k]", text) for n in re.findall(r'"(k_\w+)"', call))
+    assert "k_osd_retry" in names["osd.hip"] and "k_bp_dev" in names["decode.hip"]
+    errors = {"k_count_errors"}                                   # the error count has no share in either
+    for f in ("decode.hip", "osd.hip", "bp_chunk.hip", "bp_stream.hip", "bp_lanes.hip", "bp_fused.hip"):
+        assert names[f] and names[f] - errors <= set(bench.DECODE_KERNELS), (f, names[f])
+    assert names["sample.hip"] and all(n.startswith(bench.SAMPLE_KERNELS) for n in names["sample.hip"])
+    kern = {"k_osd": (2, 3.0), "k_osd_sort": (2, 1.0), "k_frame": (1, 5.0)}
+    assert bench.decode_ms_of(kern) == 4.0 and bench.sample_ms_of(kern) == 5.0
