@@ -78,7 +78,8 @@ WRITE_SCALE = 1048576.0 / 1048576.0
 WEIGHTS_DIR = os.path.join(ROOT, "paper_2504_05611_amd", "weights")
 SAMPLE_KERNELS = ("k_event", "k_scan", "k_frame", "k_zero_u32")
 DECODE_KERNELS = ("k_bp", "k_bp_stream", "k_bp_dev", "k_bp_lanes", "k_osd", "k_osd_sort", "k_osd_retry", "k_compact",
-                  "k_begin_pass", "k_finish_stats", "k_chunk_weights", "k_zero_i32", "k_synd_transpose", "k_zero_words", "k_fill_i32")
+                  "k_begin_pass", "k_finish_stats", "k_chunk_weights", "k_zero_i32", "k_synd_transpose", "k_zero_words",
+                  "k_fill_i32")
 
 
 def traffic_bytes(workload, kernel):
@@ -218,15 +219,17 @@ def roofline(kern, parts, workload):
     sec = ms / 1e3
     out = dict(kernel=dominant, avg_launch_ms=ms / launches, launches=launches)
     if dominant in ("k_bp", "k_bp_stream"):
-        streamed = dominant == "k_bp_stream"
-        # (one BP kernel for all of them, or those whose state is large and those whose state is not)
-        alone = not any(k in kern for k in ("k_bp", "k_bp_stream", "k_bp_dev", "k_bp_lanes") if k != dominant)
-        ops = sum(BP_OPS_PER_EDGE_ITER * d.edges * st["bp_iters"] for d, st, _, gs in parts if alone or bool(gs) == streamed)
-        ach = ops / sec / 1e12
+        # an instance whose state fits in LDS may be streamed all the same: where both kernels
+        # ran, their operations and times are taken together; beside a device-memory kernel the
+        # instances whose state is in device memory are left out
+        lds = [k for k in ("k_bp", "k_bp_stream") if k in kern]
+        dev = any(k in kern for k in ("k_bp_dev", "k_bp_lanes"))
+        ops = sum(BP_OPS_PER_EDGE_ITER * d.edges * st["bp_iters"] for d, st, _, gs in parts if not (dev and gs))
+        ach = ops / (sum(kern[k][1] for k in lds) / 1e3) / 1e12
         out.update(bound="alu", achieved=ach, peak=VALU_PEAK_TOPS, unit="TOP/s", frac=ach / VALU_PEAK_TOPS,
                    model=f"{BP_OPS_PER_EDGE_ITER} lane-ops per edge per BP iteration, summed over the "
-                         f"instances whose BP state is {'streamed through' if streamed else 'in'} LDS "
-                         f"({ops:.4g} lane-ops in {launches} launches)")
+                         f"instances decoded by {' and '.join(lds)} ({ops:.4g} lane-ops in "
+                         f"{sum(kern[k][0] for k in lds)} launches)")
     elif dominant == "k_bp_lanes":
         byts = sum(2 * lanes_state_bytes(d) * st["bp_iters"] for d, st, _, gs in parts if gs)
         ach = byts / sec / 1e9

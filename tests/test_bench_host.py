@@ -65,3 +65,22 @@ def test_every_kernel_counts_towards_sampling_or_decoding():
     assert names["sample.hip"] and all(n.startswith(bench.SAMPLE_KERNELS) for n in names["sample.hip"])
     kern = {"k_osd": (2, 3.0), "k_osd_sort": (2, 1.0), "k_frame": (1, 5.0)}
     assert bench.decode_ms_of(kern) == 4.0 and bench.sample_ms_of(kern) == 5.0
+
+
+def test_bp_roofline_covers_both_lds_kernels():
+    """An instance whose state fits in LDS may be streamed all the same (many shots, one
+    team per compute unit), so where both kernels ran their time is taken together."""
+    small = SimpleNamespace(rows=10, cols=50, edges=101)
+    mid = SimpleNamespace(rows=900, cols=6000, edges=12003)
+    large = SimpleNamespace(rows=9000, cols=60000, edges=120030)
+    parts = [(small, {"bp_iters": 700}, 64, False), (mid, {"bp_iters": 900}, 64, False), (large, {"bp_iters": 300}, 64, True)]
+    ops = bench.BP_OPS_PER_EDGE_ITER * sum(d.edges * st["bp_iters"] for d, st, _, _ in parts)
+    both = bench.roofline({"k_bp": (4, 1.0), "k_bp_stream": (4, 8.0), "k_osd": (4, 2.0)}, parts, [])
+    assert both["kernel"] == "k_bp_stream" and both["avg_launch_ms"] == pytest.approx(2.0)
+    assert both["achieved"] == pytest.approx(ops / 9e-3 / 1e12)
+    one = bench.roofline({"k_bp_stream": (4, 8.0), "k_osd": (4, 2.0)}, parts, [])
+    assert one["achieved"] == pytest.approx(ops / 8e-3 / 1e12)
+    # beside the device-memory kernel, which takes the large instance
+    lds = bench.BP_OPS_PER_EDGE_ITER * sum(d.edges * st["bp_iters"] for d, st, _, gs in parts if not gs)
+    beside = bench.roofline({"k_bp": (4, 8.0), "k_bp_dev": (4, 1.0)}, parts, [])
+    assert beside["achieved"] == pytest.approx(lds / 8e-3 / 1e12)
