@@ -57,19 +57,19 @@ TRAFFIC = {
         "k_bp_stream": {"src": ['paper_2504_05611_amd/csrc/kernels/bp_stream.hip',
                                 'paper_2504_05611_amd/csrc/kernels/bp_stream.h',
                                 'paper_2504_05611_amd/csrc/kernels/bp_team.h'],
-                        "sha256": "0e04daa65d34d1df40f0edf623176e3fbe243634ff4e05b5903b881a023dbf5a",
-                        "fetch_kib": 83090383.8, "write_kib": 92561194.5},
+                        "sha256": "36d0e144b8695f8377e2a2b365a6d945d899babecefcd9ca67e114e970cd4a11",
+                        "fetch_kib": 82806102.1, "write_kib": 92564245.2},
     },
     "sc5_nlcnot": {
         "k_bp": {"src": ['paper_2504_05611_amd/csrc/kernels/bp_chunk.hip',
                          'paper_2504_05611_amd/csrc/kernels/bp_chunk.h',
                          'paper_2504_05611_amd/csrc/kernels/bp_team.h'],
-                 "sha256": "d1309daaa562f45854b3cbe48d09c4fdf86aab692c95cd8be8768c84ff15757d",
-                 "fetch_kib": 45582.5, "write_kib": 115124.4},
+                 "sha256": "48cb330946943f8e7671368a58cebbfbc77dbd3ca3bc36967b005ff96261d3ad",
+                 "fetch_kib": 45601.0, "write_kib": 115120.6},
         "k_frame": {"src": ['paper_2504_05611_amd/csrc/kernels/sample.hip',
                             'paper_2504_05611_amd/csrc/host/program.cpp'],
                     "sha256": "80cb162d486ff4a927b96fd8c873057694403c61b958581820946205afd66834",
-                    "fetch_kib": 59886.8, "write_kib": 38549.5},
+                    "fetch_kib": 59877.2, "write_kib": 38549.5},
     },
 }
 FETCH_SCALE = 1048576.0 / 524302.5   # copy-kernel calibration (1 GiB read per launch)

@@ -227,7 +227,14 @@ typedef struct {
   int32_t bp_global_state;  /* where a shot's BP state lives.  0: LDS while it fits the 160 KB
                                of a compute unit, otherwise device memory, streamed through
                                LDS in tiles where the DEM's columns allow it (surface codes)
-                               and as for 1 elsewhere.  1: device
+                               and as for 1 elsewhere.  (Streaming also takes DEMs that fit
+                               with one team per compute unit, from 8 shots per unit on.  It
+                               and the faster form of the LDS kernel need |q| to stay finite:
+                               without weights, and while its bound, growing by a factor of
+                               1 + (max column degree + 1) alpha per iteration, stays below
+                               1e37 - max_iter up to 45 for the non-local CNOT, 38 for BB
+                               memory and 30 for BB teleportation at alpha = 1; beyond, as
+                               for 1, or the LDS kernel's comparisons written out.)  1: device
                                memory, one team (workgroup) per shot.  2: device memory, 64
                                shots per workgroup interleaved by lane (each wave runs one
                                record list of the Tanner graph for all 64 shots; a lane whose
@@ -284,7 +291,8 @@ typedef struct {
                                 columns (127 for DEMs whose elimination basis fits in LDS,
                                 else 1023) did not span the syndrome and that were decoded
                                 again with a full sort; the result is the dense OSD-0's
-                                either way */
+                                either way.  Windowed: shots that the first window left
+                                open and a larger one ended */
   uint64_t bp_iter_hist[TMCS_BP_HIST_BINS]; /* shots by BP iteration count: bin t < 64 counts
                                 shots that ran exactly t iterations (0: all-zero syndrome),
                                 bin 64 those that ran 64 or more */
@@ -295,7 +303,10 @@ typedef struct {
  * stats_dev (device, may be NULL) is incremented.  Work is enqueued on stream;
  * the call does not wait for it.  The DEM handle keeps device scratch that grows
  * with the shots of a pass: about 4 * cols bytes per shot for the posteriors
- * handed to OSD (at most 8 GiB; decode_chunk caps it) plus a few words per shot.
+ * handed to OSD (at most 8 GiB; decode_chunk caps it), as much again for their
+ * order with osd_order > 0 on DEMs whose elimination basis does not fit in LDS,
+ * about 10 * max_iter * edges bytes for weights laid out for a state in LDS, plus
+ * a few words per shot.
  * The first call of a kind on a handle - another BP kernel or team size, which may
  * follow from the number of shots - also builds its schedule: some milliseconds on
  * the host and a copy that waits for none of the caller's work.  That may happen
@@ -356,7 +367,8 @@ tmcs_status tmcs_wbp_backward(const tmcs_dem* d, const float* weights_dev, int32
 /* Where the forward/backward kernels keep a shot's working state: in LDS when it
  * fits in the 160 KB of a compute unit (default), else in per-workgroup slabs of
  * device memory that the library allocates.  on = 1 uses the device-memory slabs
- * always (process-wide; results are identical either way). */
+ * always (process-wide).  Posteriors are identical either way; gradients to
+ * rounding, since additions to one of them meet in no fixed order. */
 tmcs_status tmcs_wbp_global_state(int32_t on);
 
 /* Launch-shape autotuner: decodes the caller's syndromes (det_dev, n_shots

@@ -1,13 +1,14 @@
 // Min-sum BP for large graph-like DEMs (surface codes): one pass over the checks
 // per iteration, a shot's state streamed through a ring of tiles in LDS.
 //
-// What bounds it: VALU issue (about 21 instructions per edge and iteration, all
-// of it: no column pass).  Nearly every mechanism of a surface code touches two
-// detectors, and they are near each other in detector order (time, then place).
-// So a check's lane can rebuild L_v of an edge from its own state and that of
-// the one other check c' of the column, L_v = lambda_v + the two messages in
-// ascending check order, and never needs an L array: state is 12 bytes per
-// check, read and written once per iteration in whole lines.
+// What bounds it: VALU issue (about 21 instructions per edge step, all of it: no
+// column pass; 26 per edge and iteration counted, which fill 75 % of the issue slots
+// over the launch of d = 11 to 29 at two p).  Nearly every mechanism of a surface
+// code touches two detectors, and they are near each other in detector order (time,
+// then place).  So a check's lane can rebuild L_v of an edge from its own state and
+// that of the one other check c' of the column, L_v = lambda_v + the two messages
+// in ascending check order, and never needs an L array: state is 12 bytes per check,
+// read and written once per iteration in whole lines.
 //
 // Checks are cut, in detector order, into tiles of P (one check per lane), each
 // tile sorted so that the 64 checks of a wave (a chunk) have the same number of

@@ -9,23 +9,26 @@
 // w_t(c, v) per edge and iteration for weighted BP.  The paper names BP-OSD
 // (Supplementary Note 7) without its equations; these are the standard ones.
 //
-// Layout: one workgroup decodes one shot at a time (persistent loop over a
-// device queue).  Per-shot state lives in LDS in compressed form: L_v per
-// column, (min1, min2, argmin edge, sign parity, syndrome bit) per check and one
-// sign bit per edge; the messages m_{c->v} and q_{v->c} are recomputed from it,
-// never stored.  Sums over a column run in ascending check order and no
+// Layout: one workgroup (a team) decodes one shot at a time (persistent loop over a
+// device queue).  Per-shot state is kept in compressed form: per check or part of
+// one the two smallest |q|, which edge holds the minimum, s_c and the sign of the
+// message to each edge; messages m_{c->v} and q_{v->c} are recomputed from it, never
+// stored.  It sits in LDS (bp_chunk.hip, with L_v per column), is streamed through
+// LDS (bp_stream.hip, without), or is in device memory (k_bp here, bp_lanes.hip,
+// bp_fused.hip).  Sums over a column run in ascending check order and no
 // multiply-add is contracted, so results are bit-identical to an FP32 reference
 // that follows the same order.
 //
-// OSD-0 (order 0 ordered-statistics decoding): columns sorted by (L_v, v)
-// ascending (bitonic sort of 64-bit keys in LDS), the first rank(H) columns that
-// are GF(2)-independent of the ones before them are kept, and H_S e_S = s is
-// solved on them.  Elimination keeps an echelon basis of reduced columns in HBM
-// (each vector = m syndrome bits followed by rank bits recording which kept
-// columns it sums); candidates are reduced 256 at a time, one per thread, in
-// registers, then among themselves in order.  DEMs beyond 2048 detectors or
-// 16384 columns run the same elimination on a window of the sorted order (the
-// smallest keys, found by radix selection, and the detectors they touch).
+// OSD-0 (order 0 ordered-statistics decoding, osd.hip): columns sorted by (L_v, v)
+// ascending, the first rank(H) columns that are GF(2)-independent of the ones
+// before them are kept, and H_S e_S = s is solved on them.  Elimination keeps a
+// fully reduced basis of the kept columns in LDS or HBM (each vector = m syndrome
+// bits followed by bits recording which kept columns it sums).  A wave takes 63
+// candidates at a time, reduced by the basis and then by each other in order, with
+// the syndrome beside them, and stops at the column that completes its span.  DEMs
+// beyond 2048 detectors or 16384 columns run the same elimination on a window of
+// the sorted order (the smallest keys, found by radix selection, and the detectors
+// they touch).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

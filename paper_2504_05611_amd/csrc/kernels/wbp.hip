@@ -532,7 +532,8 @@ tmcs_status ensure(const Dem& D, WbpDevice** out) {
 // need, 3.5).  A call that is being captured takes no turn, since its kernels run at
 // every replay, whatever else then does; it uses neither the laid-out weights nor
 // the rows (COL, ROWS), so replays only share what a forward pass always shared,
-// its syndromes.
+// its syndromes (512 shots of the BB [[144,12,12]] teleportation, T = 20, ms: forward
+// 2.07 instead of 1.80, backward 4.35 instead of 2.20).
 struct Turn {
   WbpDevice* d;
   hipStream_t stream;
