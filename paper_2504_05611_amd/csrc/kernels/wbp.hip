@@ -406,7 +406,8 @@ __global__ void __launch_bounds__(256) k_wbp_weights(const float* __restrict__ w
 
 // gw[i] += sum over shots of rows[shot][i]; blockIdx.y takes every gridDim.y-th
 // run of SUM_RUN shots (runs, then the runs' sums: a few hundred terms never meet
-// one accumulator).
+// one accumulator).  The addition is atomic whatever the grid: the gradient is the
+// caller's, and calls on other streams or DEM handles may be adding to it.
 constexpr int SUM_RUN = 8;
 __global__ void __launch_bounds__(256) k_wbp_sum(const float* __restrict__ rows, int64_t TE, int64_t nshots,
                                                  float* gw) {
